@@ -469,7 +469,7 @@ def ncp_force_goertzel(on: bool = True):
 
 
 def fp_force_stage_share(eighths: int = -1):
-    """Eighths (0..8) of the four-angle forward blocks that stage their band rows in LDS;
+    """Eighths (0..8) of the multi-angle forward blocks that stage their band rows in LDS;
     -1 restores the automatic share (abg_fp_force_stage_share). Results are bit-identical
     for every share."""
     _check(load_library().abg_fp_force_stage_share(int(eighths)), "abg_fp_force_stage_share")

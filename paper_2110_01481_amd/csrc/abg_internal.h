@@ -211,11 +211,17 @@ void ncp_force_goertzel(int on);
 // Process-wide: forward projector block shape, 2^lg_apb angles per block (0..2), or -1 for
 // the automatic choice (tests and measurements).
 void fwd_force_block_shape(int lg_apb);
-// Forward projector block shape (log2 of the angles per block of 256 threads) for a
-// geometry: the choice single solves make, or the forced one.
-int fwd_lg_angles_per_block(const Geometry &g);
-int fwd_stage_eighths(int dtype);
-int fwd_stage_eighths(const Geometry &g, int dtype);
+// How a geometry's forward projection is launched (the choice single solves make, with
+// the forced settings applied).
+struct FwdPlan {
+    int nw;      // line model: waves (angles) per block of the staged kernel; 0: direct kernel
+    int share;   // eighths of the staged kernel's blocks that stage (8: all)
+    bool tiled;  // staged kernel: blocks dealt out in tiles, one XCD each
+    int lg;      // direct and model kernels: log2 of the angles per block of 256 threads
+};
+FwdPlan fwd_plan(const Geometry &g, int dtype);
+// Eighths of staged blocks that stage: the forced share, or all.
+int fwd_stage_share();
 void fwd_force_stage_eighths(int eighths);
 // d_k of the residual r into st->ncp; raises the NCP stop for step k when k >= 2 and
 // d_k > d_{k-1}. `snap`: as for launch_combine.

@@ -101,7 +101,7 @@ struct Tiles {
     int ang_block;   // back projectors: angles staged in LDS per round (64 or 128)
     int sched;       // item schedule of the projector and residual lists (for_each_item)
     int stage = 0;   // eighths of the four-angle forward items that stage their band rows
-                     // in LDS (set at launch from the single-solve rule)
+                     // in LDS (8, or the forced share)
 };
 
 namespace {
@@ -377,7 +377,7 @@ template <typename T>
 __global__ __launch_bounds__(256, 8) void bfwd_kernel(const BatchInst *__restrict__ D, const DevState *S,
                                                    TabView tv, int t, int mode, Tiles tl)
 {
-    __shared__ FwdStageLds<T> lds;
+    __shared__ FwdStageLds<T, 4> lds;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     for_each_item(tv, t, tl.sched, [&](int slot, int local) {
@@ -389,14 +389,15 @@ __global__ __launch_bounds__(256, 8) void bfwd_kernel(const BatchInst *__restric
         const int wpa = rays / 64;       // waves per angle
         const int apb = 256 / rays;      // angles per block
         const int nrg = (d.n_det + rays - 1) / rays;
-        // a share of the four-angle items, spread by a hash of the item, walks with its band
-        // rows staged in LDS (the whole block, before any wave leaves)
+        // four-angle items (or a forced share of them, spread by a hash of the item) walk with
+        // their band rows staged in LDS (the whole block, before any wave leaves)
         if (rays == 64 && tl.stage > 0 &&
             (int)(((unsigned)local * 0x9E3779B1u + (unsigned)slot * 0x85EBCA6Bu) >> 29) < tl.stage) {
             T *y = mode == 0 ? zcol<T>(d, k) : gfield<T>(d.q);
-            forward_block_staged(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
-                                 gfield<const AngleParams>(d.ang), (local / nrg) * 4,
-                                 (local % nrg) * 64, d.N, d.S, d.n_ang, d.n_det, d.ds, d.s0, lds);
+            forward_block_staged<T, 4>(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
+                                       gfield<const AngleParams>(d.ang), (local / nrg) * 4,
+                                       (local % nrg) * 64, d.N, d.S, d.n_ang, d.n_det, d.ds, d.s0,
+                                       lds);
             return;
         }
         const int a = (local / nrg) * apb + wave / wpa;
@@ -786,7 +787,7 @@ struct Engine {
     {
         begin_kernel<<<kNumTab, 256, 0, q>>>(d_desc, d_st, tv, max_slots, tl);
         Tiles tf = tl;
-        tf.stage = fwd_stage_eighths(p.proj);
+        tf.stage = fwd_stage_share();
         hipStream_t qa = q;
         if (q2) {
             (void)hipEventRecord(fork_ev, q);
@@ -934,7 +935,8 @@ struct Engine {
         d.count = v.count;
         d.bd_rel = (p.basis == ABG_F64 && p.proj == ABG_F64) ? 1e-14 : 1e-6;
         d.need_res = r.stop.kind == ABG_STOP_DP;
-        d.fwd_rays = 256 >> fwd_lg_angles_per_block(g);
+        const FwdPlan fp = fwd_plan(g, p.proj);
+        d.fwd_rays = fp.nw > 0 ? 64 : 256 >> fp.lg;
         // Gram-Schmidt class: the smallest register tile whose block group the device
         // holds at once (the small tile while its group stays small), else the streaming
         // variant. A group must be resident as a whole: its size stays within the

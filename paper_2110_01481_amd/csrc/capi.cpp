@@ -72,7 +72,7 @@ AngleParams make_angle(double theta_deg, double ds)
     P.inv = P.steep ? 1.0 / c : 1.0 / s;
     P.len = 1.0 / P.p;
     P.axis = P.q == 0.0 ? 1 : 0;
-    P.invq = P.axis ? 0.0 : 1.0 / P.q;
+    P.pq = P.axis ? 0.0 : std::fmin(P.p / P.q, 1e30);
     if (P.axis) P.m = 0.0;
     P.cu = c / ds;
     P.su = s / ds;

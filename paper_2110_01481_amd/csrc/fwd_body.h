@@ -4,6 +4,7 @@
 #pragma once
 
 #include <cmath>
+#include <type_traits>
 
 #include "abg_internal.h"
 #include "footprint.h"
@@ -68,46 +69,78 @@ __device__ inline void pad_zero_item(T *__restrict__ xr, T *__restrict__ xc, int
     base[col] = T(0);
 }
 
+// Bands of a forward walk are taken in groups of kChunk consecutive bands that start at a
+// multiple of kChunk.
+constexpr int kChunk = 8;
+
 // Position of a ray inside the current band of pixels: the band holds the minor-axis
-// interval [lo, lo + |m|] (pixels from the image edge) and the walk advances lo by m.
-// FP64 data: lo in FP64. FP32 data: lo biased by kPad as an integer column and a 32-bit
-// fraction, so a band step is an add with carry, the pixel index is the integer part and
-// the fraction gives the weight.
+// interval [lo, lo + |m|] (padded columns, + kPad) and the walk advances lo by m. A walk
+// may start at any multiple of kChunk: the position in a band does not depend on where
+// the walk began (FP64: formed anew from the band number at every multiple of kChunk;
+// FP32: exact integer steps), so that every way of walking a ray gives the same bits.
+// FP64 data: lo in FP64. FP32 data: lo as an integer column and a 32-bit fraction, so a
+// band step is an add with carry, the pixel index is the integer part and the fraction
+// gives the weight.
 template <typename T> struct Band;
+// Share of a band segment that lies left of the pixel edge it crosses: the segment is 1/p
+// long and the part left of the edge (1 - frac) / q, so the share is
+// min(1, (1 - frac) p/q). One multiply-add with the output clamped to [0, 1]; the length
+// 1/p is a common factor of the whole ray.
 template <typename T> struct BandWeights {
-    T invq, len;
-    __device__ BandWeights(double iq, double l) : invq(T(iq)), len(T(l)) {}
+    T pq;
+    __device__ explicit BandWeights(double pq_) : pq(T(pq_)) {}
+};
+
+// Sum of a ray's taps. FP32: the bands of a group are summed in FP32 and the groups in FP64.
+// A single FP32 sum would round every pixel a ray crosses whole (share 1) to the sum's last
+// place, alike for all rays through it: small, but coherent over the angles, and a solve
+// amplifies such an error where it averages out independent ones.
+template <typename T> struct RaySum {
+    T part = T(0);
+    double all = 0.0;
+    __device__ void tap(T w, T v) { part = fma(w, v, part); }
+    __device__ void group_done()
+    {
+        if constexpr (sizeof(T) == 4) {
+            all += (double)part;
+            part = T(0);
+        }
+    }
+    __device__ T times(double len) const
+    {
+        if constexpr (sizeof(T) == 4) return T(all * len);
+        else return part * len;
+    }
 };
 
 template <> struct Band<double> {
-    // lo: the band's lower minor-axis edge in padded column coordinates (+ kPad), so that
-    // floor(lo) is the padded column itself
-    double lo, m;
-    __device__ Band(double lo0, double m_) : lo(lo0 + kPad), m(m_) {}
+    double lo0, m, lo;
+    // lo0_: lower minor-axis edge of band 0, in pixels from the image edge; floor(lo) is
+    // the padded column itself
+    __device__ Band(double lo0_, double m_) : lo0(lo0_ + kPad), m(m_), lo(lo0) {}
+    __device__ void seek(int r) { lo = fma((double)r, m, lo0); }
+    __device__ void rebase(int r) { seek(r); }
     __device__ void next() { lo += m; }
     __device__ unsigned column(unsigned cmax) const
     {
         return min((unsigned)(int)floor(lo), cmax);
     }
-    // padded column, unclamped, by truncation. A wave walks only the bands some lane's
-    // ray crosses (at most N of them, |m| <= 1), and the lanes of a wave lie within 63
-    // bins of each other (63 * 64 * sqrt(2) < 5702 px for the spacings a geometry
-    // accepts), so every column a walking lane reaches is below 2N + 5710 < 2^17 in
+    // padded column, unclamped, by truncation. A wave walks only bands near those some
+    // lane's ray crosses (at most N of them, |m| <= 1), and the lanes of a wave lie within
+    // 63 bins of each other (63 * 64 * sqrt(2) < 5702 px for the spacings a geometry
+    // accepts), so every column a walking lane reaches is below 2N + 5720 < 2^17 in
     // magnitude (N <= 32768): the conversion is exact and the byte offset cannot wrap back
     // into the row. A tap can meet a nonzero pixel only for lo >= kPad - 1 > 0, where
     // truncation is floor; below, truncation lands in the zero padding (lo > -1) or before
     // the row (out of range, read as zero) as floor would.
     __device__ int column_raw() const { return (int)lo; }
-    // length of the band segment left of the pixel edge at floor(lo) + 1, from the
-    // fractional part of lo (exactly lo - floor(lo) for lo >= 0)
-    __device__ double left_length(const BandWeights<double> &b) const
+    // share of the band segment left of the pixel edge at floor(lo) + 1, from the
+    // fractional part of lo (exactly lo - floor(lo) for lo >= 0). p/q is the same in every
+    // lane (a wave walks one angle), so a scalar operand holds it.
+    __device__ double left_share(const BandWeights<double> &b) const
     {
-        const double t = fma(-__builtin_amdgcn_fract(lo), b.invq, b.invq);
-        // min of two finite values: the plain instruction (fmin would quieten the
-        // loop-invariant operand on every step); the length is the same in every lane
-        // (a wave walks one angle), so a scalar operand holds it
         double w;
-        asm("v_min_f64 %0, %1, %2" : "=v"(w) : "s"(b.len), "v"(t));
+        asm("v_fma_f64 %0, -%1, %2, %2 clamp" : "=v"(w) : "v"(__builtin_amdgcn_fract(lo)), "s"(b.pq));
         return w;
     }
     // (lo - floor(lo)) * s
@@ -115,22 +148,29 @@ template <> struct Band<double> {
 };
 
 template <> struct Band<float> {
-    // lo + kPad = c + f / 2^32: integer column and 32-bit fraction, stepped by the split
-    // slope (mi, mf) with one add and one add-with-carry; error < 1e-6 px after 2^12 steps
+    // lo = c + f / 2^32 in 32.32 fixed point, stepped by the split slope (mi, mf) with one
+    // add and one add-with-carry; the slope is within 2^-33 px, so the position within
+    // 1e-6 px after 2^12 bands
     int c;
     unsigned f;
     int mi;
     unsigned mf;
+    long long p0, ms;
     __device__ Band(double lo0, double m)
+        : p0(__double2ll_rn((lo0 + kPad) * 0x1p32)), ms(__double2ll_rn(m * 0x1p32))
     {
-        const double p = lo0 + kPad;
-        const double pc = floor(p);
-        c = (int)pc;
-        f = (unsigned)min(__double2ull_rn((p - pc) * 0x1p32), 0xffffffffull);
-        const double mc = floor(m);
-        mi = (int)mc;
-        mf = (unsigned)min(__double2ull_rn((m - mc) * 0x1p32), 0xffffffffull);
+        mi = (int)(ms >> 32);
+        mf = (unsigned)ms;
+        c = (int)(p0 >> 32);
+        f = (unsigned)p0;
     }
+    __device__ void seek(int r)
+    {
+        const unsigned long long p = (unsigned long long)p0 + (unsigned long long)r * (unsigned long long)ms;
+        c = (int)(p >> 32);
+        f = (unsigned)p;
+    }
+    __device__ void rebase(int) {}
     __device__ void next()
     {
         const unsigned nf = f + mf;
@@ -142,10 +182,9 @@ template <> struct Band<float> {
         return (unsigned)min(max(c, 0), (int)cmax);
     }
     __device__ int column_raw() const { return c; }
-    __device__ float left_length(const BandWeights<float> &b) const
+    __device__ float left_share(const BandWeights<float> &b) const
     {
-        const float w = fmaf((float)f, -b.invq * 0x1p-32f, b.invq);
-        return __builtin_amdgcn_fmed3f(w, b.len, -1e30f);   // min(w, len)
+        return __builtin_amdgcn_fmed3f(fmaf((float)f, -b.pq * 0x1p-32f, b.pq), 0.f, 1.f);
     }
     // fractional part times s * 2^32 (the caller folds 2^-32 into s)
     __device__ float frac_scaled(float s) const { return (float)f * s; }
@@ -183,6 +222,12 @@ __device__ inline Taps<T> load_taps_row(const T *row, int S, int col)
 
 // Ray i of angle a (i may exceed n_det: such lanes only take part in the wave's band
 // range and store nothing). Called by whole waves of consecutive rays.
+//
+// A group of bands per trip, their loads issued before their use: this walk serves
+// launches of few waves and, among staged blocks, those whose angles lie far apart, which
+// both wait on the gather latency (512^2 x 60 angles: 87 us with two bands per trip, 40 with
+// eight; a launch that fills the device many times over is better off with two, 3.2 against
+// 3.9 ms at 2048^2 x 1800 in FP64, but it stages its rows).
 template <typename T>
 __device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict__ xc,
                                    T *__restrict__ y, const AngleParams *__restrict__ ang, int a,
@@ -214,12 +259,25 @@ __device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict
         }
         if (u0 < lo_clamp || u0 > hi_clamp) c0 = -kPad;   // outside: read zero padding
         c0 = min(max(c0, -kPad), N + kPad - 2);           // both taps inside the padded row
-        const T *p = img + c0;
-        for (int r = 0; r < N; ++r) {
-            acc = fma(w0, p[0], acc);
-            acc = fma(w1, p[1], acc);
-            p += S;
+        // a group of rows per trip, their loads issued before their use (one row at a time,
+        // the few axis-parallel angles would outlast the rest of a launch); rows past the
+        // image read as zero
+        const T *row = img - kPad;
+        RaySum<T> sum;
+        for (int r = 0; r < N; r += kChunk) {
+            Taps<T> t[kChunk];
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j)
+                t[j] = load_taps_row(row + (size_t)j * S, r + j < N ? S : 0, c0 + kPad);
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j) {
+                sum.tap(w0, t[j].a);
+                sum.tap(w1, t[j].b);
+            }
+            sum.group_done();
+            row += kChunk * (size_t)S;
         }
+        acc = sum.times(1.0);                          // w0, w1 hold the length
     } else {
         // Band r holds the minor-axis interval [lo_r, lo_r + |m|], lo_r = lo0 + r*m.
         const double lo0 = u0 + fmin(P.m, 0.0);
@@ -240,51 +298,42 @@ __device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict
             r0 = N;
             r1 = 0;
         }
-        // wave-uniform band range: lanes outside their own chord read zero padding
-        const int wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0));
+        // wave-uniform band range, from a multiple of kChunk: lanes outside their own chord
+        // read zero padding
+        const int wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0)) & ~(kChunk - 1);
         const int wr1 = __builtin_amdgcn_readfirstlane(wave_max_i(r1));
-        Band<T> band(fma((double)wr0, P.m, lo0), P.m);
+        Band<T> band(lo0, P.m);
+        band.seek(wr0);
         // row-start pointer (padding included); taps outside the padded row read zero
         const T *row = img - kPad + (size_t)wr0 * S;
-        const BandWeights<T> bw(P.invq, P.len);
-        int r = wr0;
-        // kTrip bands per trip, their loads issued before their use. Two is the measured
-        // best on gfx950 (FP64 at 2048^2: 15% below four; one and three are slower, FP32
-        // is flat): a deeper trip holds more registers in flight without more memory
-        // parallelism, since eight resident waves per SIMD already cover the gather
-        // latency.
-        constexpr int kTrip = 2;
-        for (; r + kTrip <= wr1; r += kTrip) {
-            int c[kTrip];
-            T w[kTrip], v0[kTrip], v1[kTrip];
+        const BandWeights<T> bw(P.pq);
+        RaySum<T> sum;
+        for (int r = wr0; r < wr1; r += kChunk) {
+            int c[kChunk];
+            T w[kChunk], v0[kChunk], v1[kChunk];
+            band.rebase(r);
 #pragma unroll
-            for (int j = 0; j < kTrip; ++j) {
+            for (int j = 0; j < kChunk; ++j) {
                 c[j] = band.column_raw();
-                w[j] = band.left_length(bw);
+                w[j] = band.left_share(bw);
                 band.next();
             }
+            // bands past the image read as zero
 #pragma unroll
-            for (int j = 0; j < kTrip; ++j) {
-                const Taps<T> t = load_taps_row(row + (size_t)j * S, S, c[j]);
+            for (int j = 0; j < kChunk; ++j) {
+                const Taps<T> t = load_taps_row(row + (size_t)j * S, r + j < N ? S : 0, c[j]);
                 v0[j] = t.a;
                 v1[j] = t.b;
             }
 #pragma unroll
-            for (int j = 0; j < kTrip; ++j) {
-                acc = fma(w[j], v0[j], acc);
-                acc = fma(bw.len - w[j], v1[j], acc);
+            for (int j = 0; j < kChunk; ++j) {
+                sum.tap(w[j], v0[j]);
+                sum.tap(T(1) - w[j], v1[j]);
             }
-            row += kTrip * (size_t)S;
+            sum.group_done();
+            row += kChunk * (size_t)S;
         }
-        for (; r < wr1; ++r) {
-            const int c = band.column_raw();
-            const T w = band.left_length(bw);
-            band.next();
-            const Taps<T> t = load_taps_row(row, S, c);
-            acc = fma(w, t.a, acc);
-            acc = fma(bw.len - w, t.b, acc);
-            row += S;
-        }
+        acc = sum.times(P.len);
     }
     if (i < n_det) y[(size_t)a * n_det + i] = acc;
 }
@@ -482,26 +531,25 @@ __device__ inline void forward_ray_strip(const T *__restrict__ xr, const T *__re
 // every band row in all four waves, so here each band row's columns the block can touch
 // are copied once into LDS by one 16-byte load per lane (a quarter of the addresses), and
 // the waves read their taps from there. Everything else is the walk above, band by band
-// in the same order: the results are the same bits. The LDS returns a band's taps no
-// faster than the texture path does, so this walk alone is slower; run beside the
-// direct walk in the same launch it takes its taps through the other unit.
+// in the same order: the results are the same bits. Run beside the direct walk in the
+// same launch it takes its taps through the other unit.
 //
-// The window of band r starts at org(r) and holds kStageCols columns. For angle i the
+// The window of a group of kChunk bands holds kStageCols columns from org. For angle i the
 // leftmost lane sits at lmin_i + r m_i and the rightmost at rmax_i + r m_i (padded
 // columns; lanes are monotone in their offset), so the columns the block touches lie in
 // [min_i(lmin_i + r m_i), max_i(rmax_i + r m_i) + 2]. The lower edge is concave in r and
-// the upper convex, so their chords over the block's bands bound them from below and
-// from above, and the window's width is checked at the two end bands only. org(r)
-// follows the lower chord in 32.32 fixed point on the scalar unit. Blocks whose angles
+// the upper convex, so their chords over the block's bands bound them from below and from
+// above. org is 2 below the lower chord's least value in the group (32.32 fixed point on
+// the scalar unit, once per group: the walk itself then needs no scalar work per band,
+// which used to bound it at one scalar instruction per cycle and CU). Blocks whose angles
 // differ in orientation, include an axis-aligned or a missing angle, or need a wider
 // window take the walk above.
-constexpr int kStageBands = 8;
 template <typename T> constexpr int kStageCols = 64 * 16 / (int)sizeof(T);
 
-template <typename T> struct FwdStageLds {
-    T win[2][kStageBands][kStageCols<T>];
-    double lmin[4], rmax[4], m[4];
-    int r0[4], r1[4], kind[4];
+template <typename T, int NW> struct FwdStageLds {
+    T win[2][kChunk][kStageCols<T>];
+    double lmin[NW], rmax[NW], m[NW];
+    int r0[NW], r1[NW], kind[NW];
 };
 
 __device__ inline double lane_value_f64(double v, int l)
@@ -521,13 +569,14 @@ __device__ inline long long uniform_ll(long long v)
 // Angles a0 .. a0 + 3 (wave w takes a0 + w), rays ray0 .. ray0 + 63 of each. All four
 // waves call it (also for angles past n_ang); it starts with a block-wide barrier, so
 // that consecutive calls of a block may share L.
-template <typename T>
+template <typename T, int NW>
 __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *__restrict__ xc,
                                             T *__restrict__ y, const AngleParams *__restrict__ ang,
                                             int a0, int ray0, int N, int S, int n_ang, int n_det,
-                                            double ds, double s0, FwdStageLds<T> &L)
+                                            double ds, double s0, FwdStageLds<T, NW> &L)
 {
     constexpr int W = kStageCols<T>;
+    constexpr int kB = (int)sizeof(T);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int a = a0 + wave, i = ray0 + lane;
@@ -544,7 +593,7 @@ __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *_
             lo0 = u0 + fmin(P.m, 0.0);
             int r0, r1;
             band_range(lo0, P.m, N, 0.0, i < n_det, r0, r1);
-            wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0));
+            wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0)) & ~(kChunk - 1);
             wr1 = __builtin_amdgcn_readfirstlane(wave_max_i(r1));
             const double l0 = lane_value_f64(lo0, 0), l63 = lane_value_f64(lo0, 63);
             lmin = fmin(l0, l63) + kPad;
@@ -562,27 +611,34 @@ __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *_
         L.m[wave] = m;
     }
     __syncthreads();
-    // the block's choice, the same in every wave
+    // the block's choice, the same in every wave; bands rb0 .. rb1 - 1, whole groups as far
+    // as the image goes
     bool staged = L.kind[0] != 0;
     int rb0 = N, rb1 = 0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < NW; ++v) {
         staged = staged && L.kind[v] == L.kind[0];
-        rb0 = min(rb0, L.r0[v]);
-        rb1 = max(rb1, L.r1[v]);
+        if (L.r0[v] < L.r1[v]) {
+            rb0 = min(rb0, L.r0[v]);
+            rb1 = max(rb1, L.r1[v]);
+        }
     }
-    double lb = 1e300, le = 1e300, hb = -1e300, he = -1e300;
+    rb0 = __builtin_amdgcn_readfirstlane(rb0);
+    rb1 = __builtin_amdgcn_readfirstlane(min(N, (rb1 + kChunk - 1) & ~(kChunk - 1)));
+    double lb = 1e300, le = 1e300, hb = -1e300, he = -1e300, slope = 0.0;
     if (staged && rb0 < rb1) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < NW; ++v) {
             lb = fmin(lb, fma((double)rb0, L.m[v], L.lmin[v]));
             le = fmin(le, fma((double)(rb1 - 1), L.m[v], L.lmin[v]));
             hb = fmax(hb, fma((double)rb0, L.m[v], L.rmax[v]));
             he = fmax(he, fma((double)(rb1 - 1), L.m[v], L.rmax[v]));
         }
-        // taps reach 2 columns right of a lane's position (truncation of a negative
-        // position adds one); org sits 2 below the lower chord
-        staged = fmax(hb - lb, he - le) + 6.0 <= (double)W;
+        slope = rb1 - 1 > rb0 ? (le - lb) / (double)(rb1 - 1 - rb0) : 0.0;
+        // over a group the lower chord moves by at most (kChunk - 1) |slope|; taps reach 2
+        // columns right of a lane's position (truncation of a negative position adds one);
+        // org sits 2 below the lower chord
+        staged = fmax(hb - lb, he - le) + (kChunk - 1) * fabs(slope) + 6.0 <= (double)W;
     }
     if (!staged) {
         if (a < n_ang) forward_ray(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
@@ -591,47 +647,77 @@ __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *_
     T acc = T(0);
     if (rb0 < rb1) {
         const T *img = L.kind[0] == 1 ? xr : xc;       // padded rows
-        const double slope = rb1 - 1 > rb0 ? (le - lb) / (double)(rb1 - 1 - rb0) : 0.0;
-        const long long ofx0 = uniform_ll(__double2ll_rn((lb - 2.0) * 0x1p32));
         const long long dfx = uniform_ll(__double2ll_rn(slope * 0x1p32));
-        auto org_of = [&](int r) { return (int)((ofx0 + (long long)(r - rb0) * dfx) >> 32); };
-        auto stage = [&](int cb, int par) {
+        // least value of the chord over the group that starts at rb0
+        long long ofx = uniform_ll(__double2ll_rn((lb - 2.0) * 0x1p32)) +
+                        (dfx < 0 ? (kChunk - 1) * dfx : 0);
+        auto stage = [&](int cb, int par, int org) {
 #pragma unroll
-            for (int q = 0; q < kStageBands / 4; ++q) {
-                const int r = cb + wave + 4 * q;
+            for (int q = 0; q < kChunk / NW; ++q) {
+                const int j = wave + NW * q, r = cb + j;
                 if (r < rb1) {
                     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                        const_cast<T *>(img + (size_t)r * S), (short)0, S * (int)sizeof(T),
-                        kRawBufferFlags);
+                        const_cast<T *>(img + (size_t)r * S), (short)0, S * kB, kRawBufferFlags);
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                        rs, (__attribute__((address_space(3))) void *)&L.win[par][r - cb][0], 16,
-                        org_of(r) * (int)sizeof(T) + lane * 16, 0, 0, 0);
+                        rs, (__attribute__((address_space(3))) void *)&L.win[par][j][0], 16,
+                        org * kB + lane * 16, 0, 0, 0);
                 }
             }
         };
-        Band<T> band(fma((double)wr0, P.m, lo0), P.m);
-        const BandWeights<T> bw(P.invq, P.len);
-        stage(rb0, 0);
+        using LdsT = __attribute__((address_space(3))) const T;
+        using LdsC = __attribute__((address_space(3))) const char;
+        Band<T> band(lo0, P.m);
+        const BandWeights<T> bw(P.pq);
+        RaySum<T> sum;
+        int org = (int)(ofx >> 32);
+        stage(rb0, 0, org);
         int par = 0;
-        for (int cb = rb0; cb < rb1; cb += kStageBands, par ^= 1) {
+        for (int cb = rb0; cb < rb1; cb += kChunk, par ^= 1) {
             __builtin_amdgcn_s_waitcnt(0);                 // this wave's rows have landed
             __syncthreads();                               // every wave's rows, and the other
                                                            // buffer is free again
-            if (cb + kStageBands < rb1) stage(cb + kStageBands, par ^ 1);
-            const int e0 = max(cb, wr0), e1 = min(cb + kStageBands, wr1);
-            for (int r = e0; r < e1; ++r) {
-                const int c = band.column_raw();
-                const T w = band.left_length(bw);
-                band.next();
-                // the column within the window as one vector value (kept whole, so that
-                // both taps come from one address)
-                int off = c - org_of(r);
-                asm volatile("" : "+v"(off));
-                const Taps<T> t = *reinterpret_cast<const Taps<T> *>(&L.win[par][r - cb][off]);
-                acc = fma(w, t.a, acc);
-                acc = fma(bw.len - w, t.b, acc);
+            ofx += kChunk * dfx;
+            const int nxt = (int)(ofx >> 32);
+            if (cb + kChunk < rb1) stage(cb + kChunk, par ^ 1, nxt);
+            band.seek(cb);
+            // one scalar base per group: a band's tap is at base + column, its row at a
+            // constant offset
+            LdsC *win = (LdsC *)&L.win[par][0][0] - org * kB;
+            // the taps of G bands are read before the first is used; FP64 takes a band's two
+            // taps with two 8-byte reads, kept apart (one read2 of adjacent values costs
+            // half as much again: 16.4 cycles of the CU's LDS against 10.4 for a wave)
+            auto taps = [&](auto G_, int j0) {
+                constexpr int G = decltype(G_)::value;
+                T w[G], ta[G], tb[G];
+#pragma unroll
+                for (int j = 0; j < G; ++j) {
+                    // the byte offset kept whole, so that both taps come from one address
+                    unsigned at = (unsigned)(size_t)win + (unsigned)band.column_raw() * (unsigned)kB;
+                    asm volatile("" : "+v"(at));
+                    w[j] = band.left_share(bw);
+                    band.next();
+                    LdsT *t = (LdsT *)(size_t)(at + (unsigned)((j0 + j) * W * kB));
+                    ta[j] = t[0];
+                    if constexpr (kB == 8) asm volatile("" ::: "memory");
+                    tb[j] = t[1];
+                }
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int j = 0; j < G; ++j) {
+                    sum.tap(w[j], ta[j]);
+                    sum.tap(T(1) - w[j], tb[j]);
+                }
+            };
+            if (cb + kChunk <= rb1) {
+#pragma unroll
+                for (int j = 0; j < kChunk; j += 4) taps(std::integral_constant<int, 4>{}, j);
+            } else {
+                for (int j = 0; j < rb1 - cb; ++j) taps(std::integral_constant<int, 1>{}, j);
             }
+            sum.group_done();
+            org = nxt;
         }
+        acc = sum.times(P.len);
     }
     if (a < n_ang && i < n_det) y[(size_t)a * n_det + i] = acc;
 }

@@ -19,7 +19,7 @@ struct AngleParams {
     double m;           // -s/c (steep) or -c/s (flat)
     double inv;         // 1/c (steep) or 1/s (flat)
     double len;         // 1/p
-    double invq;        // 1/q (0 when q == 0)
+    double pq;          // min(p/q, 1e30) (0 when q == 0)
     // pixel-driven back projectors: detector coordinate u = <c_j, omega>/ds - s0/ds
     double cu, su;      // cos/ds, sin/ds: change of u per pixel step in x and in y
     double half;        // (p+q)/2: half-width of the line-model trapezoid

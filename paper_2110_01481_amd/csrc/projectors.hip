@@ -75,27 +75,59 @@ __global__ __launch_bounds__(kFwdBlock) void forward_kernel(
     forward_ray(xr, xc, y, ang, a, sh.lane_ray(wave), N, S, n_det, ds, s0);
 }
 
-// Line model, four angles per block: a share of the blocks (stage_eighths of every 8,
-// spread over the grid by a hash of the block index) walk with their band rows staged in
-// LDS, the others take their taps straight from the image copies.
-template <typename T>
-__global__ __launch_bounds__(kFwdBlock) void forward_mixed_kernel(
+// Order of the blocks of a staged launch: ngx ray groups (64 rays) by ngy angle groups (NW
+// angles). With rows == 0 the ray group runs fastest. Otherwise the blocks come in tiles of
+// one ray group by `rows` angle groups, dealt out to the eight XCDs (blocks b with equal b
+// mod 8 run on one XCD), the ray group fastest within a row of tiles: the blocks an XCD
+// holds at one time then walk nearly the same image pixels, which stay in its 4 MB L2.
+// `cols`, the tiles of a row, is ngx padded to 2 mod 4: the XCDs move on by 2 or 6 ray
+// groups from one row of tiles to the next and so share long (central) and short rays
+// evenly over the kFwdTileRows rows. Tiles and blocks past the ends leave at once.
+struct FwdOrder {
+    int ngx, ngy, rows, cols;
+    __device__ bool block(int b, int &gx, int &gy) const
+    {
+        if (rows == 0) {
+            gy = b / ngx;
+            gx = b - gy * ngx;
+            return true;
+        }
+        const int i = b >> 3, j = i / rows;
+        const int t = 8 * j + (b & 7), tr = t / cols;
+        gx = t - tr * cols;
+        gy = tr * rows + (i - j * rows);
+        return gx < ngx && gy < ngy;
+    }
+};
+constexpr int kFwdTileRows = 4;
+
+// Line model, NW angles per block, band rows staged in LDS (forward_block_staged): bound by
+// the VALU (8 instructions per band, wave and ray; 83% busy at 2048^2 x 1800 in FP64) beside
+// 8 cycles of LDS reads per band and wave. 2048^2 x 1800 x 2897: FP64 3.20 -> 2.07 ms, FP32
+// 2.77 -> 1.58 ms against the direct walk with the staged share it had; L2 fills 15.4 -> 5.0 GB
+// (FP64), gathers 1.1e8 -> 1.6e7 per launch. A share
+// of the blocks below eight eighths (tests and measurements; spread over the grid by a hash
+// of the block) stages, the others take their taps straight from the image copies.
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void forward_staged_kernel(
     const T *__restrict__ xr, const T *__restrict__ xc, T *__restrict__ y,
     const AngleParams *__restrict__ ang, int N, int S, int n_ang, int n_det, double ds,
-    double s0, const DevState *st, int k, int stage_eighths)
+    double s0, const DevState *st, int k, int stage_eighths, FwdOrder ord)
 {
     if (halted(st, k)) return;
-    __shared__ FwdStageLds<T> lds;
-    const unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+    __shared__ FwdStageLds<T, NW> lds;
+    int gx, gy;
+    if (!ord.block(blockIdx.x, gx, gy)) return;
+    const unsigned b = (unsigned)(gy * ord.ngx + gx);
     if ((int)((b * 0x9E3779B1u) >> 29) < stage_eighths) {
-        forward_block_staged(xr, xc, y, ang, blockIdx.y * 4, blockIdx.x * 64, N, S, n_ang, n_det,
-                             ds, s0, lds);
+        forward_block_staged<T, NW>(xr, xc, y, ang, gy * NW, gx * 64, N, S, n_ang, n_det, ds, s0,
+                                    lds);
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int a = blockIdx.y * 4 + wave;
+    const int a = gy * NW + wave;
     if (a >= n_ang) return;
-    forward_ray(xr, xc, y, ang, a, blockIdx.x * 64 + ((int)threadIdx.x & 63), N, S, n_det, ds, s0);
+    forward_ray(xr, xc, y, ang, a, gx * 64 + ((int)threadIdx.x & 63), N, S, n_det, ds, s0);
 }
 
 // Strip (MODEL = ABG_FP_STRIP) and interpolation (ABG_FP_JOSEPH) models.
@@ -167,30 +199,35 @@ hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStr
             pad_zero_kernel<T><<<(npad + 255) / 256, 256, 0, s>>>(xr, xc, N, S, st, k);
         }
     }
-    const FwdShape sh{fwd_lg_angles_per_block(g)};
-    const int apb = 1 << sh.lg_apb, rays = kFwdBlock >> sh.lg_apb;
-    dim3 grid((g.n_det + rays - 1) / rays, (g.n_ang + apb - 1) / apb);
+    const FwdPlan plan = fwd_plan(g, sizeof(T) == 8 ? ABG_F64 : ABG_F32);
     const double s0 = -0.5 * (g.n_det - 1) * g.ds;
-    const int stage = fwd_stage_eighths(g, sizeof(T) == 8 ? ABG_F64 : ABG_F32);
-    if (sh.lg_apb == 2 && g.model == ABG_FP_LINE && stage > 0) {
-        ProfScope ps(kProfFwd, s, st ? k : 0, true);
-        hipExtLaunchKernelGGL(forward_mixed_kernel<T>, grid, dim3(kFwdBlock), 0, s, ps.e0, ps.e1, 0,
+    // timed at the kernel's own start and end when profiling is on
+    ProfScope ps(kProfFwd, s, st ? k : 0, true);
+    if (g.model == ABG_FP_LINE && plan.nw > 0) {
+        FwdOrder ord{(g.n_det + 63) / 64, (g.n_ang + plan.nw - 1) / plan.nw, 0, 0};
+        size_t blocks = (size_t)ord.ngx * ord.ngy;
+        if (plan.tiled) {
+            ord.rows = (ord.ngy + kFwdTileRows - 1) / kFwdTileRows;
+            ord.cols = ord.ngx + (6 - ord.ngx % 4) % 4;
+            blocks = ((size_t)ord.cols * kFwdTileRows + 7) / 8 * 8 * ord.rows;
+        }
+        auto fn = plan.nw == 8 ? forward_staged_kernel<T, 8> : forward_staged_kernel<T, 4>;
+        hipExtLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(64 * plan.nw), 0, s, ps.e0, ps.e1, 0,
                               (const T *)xr, (const T *)xc, static_cast<T *>(y),
                               (const AngleParams *)g.dev, N, S, g.n_ang, g.n_det, g.ds, s0, st, k,
-                              stage);
+                              plan.share, ord);
         return hipGetLastError();
     }
-    {
-        // timed at the kernel's own start and end when profiling is on
-        ProfScope ps(kProfFwd, s, st ? k : 0, true);
-        auto fn = g.model == ABG_FP_STRIP    ? forward_model_kernel<T, ABG_FP_STRIP>
-                  : g.model == ABG_FP_JOSEPH ? forward_model_kernel<T, ABG_FP_JOSEPH>
-                                             : forward_kernel<T>;
-        hipExtLaunchKernelGGL(fn, grid, dim3(kFwdBlock), 0, s, ps.e0, ps.e1, 0,
-                              (const T *)xr, (const T *)xc, static_cast<T *>(y),
-                              (const AngleParams *)g.dev, N, S, g.n_ang, g.n_det, g.ds, s0, st,
-                              k, sh);
-    }
+    const FwdShape sh{plan.lg};
+    const int apb = 1 << sh.lg_apb, rays = kFwdBlock >> sh.lg_apb;
+    dim3 grid((g.n_det + rays - 1) / rays, (g.n_ang + apb - 1) / apb);
+    auto fn = g.model == ABG_FP_STRIP    ? forward_model_kernel<T, ABG_FP_STRIP>
+              : g.model == ABG_FP_JOSEPH ? forward_model_kernel<T, ABG_FP_JOSEPH>
+                                         : forward_kernel<T>;
+    hipExtLaunchKernelGGL(fn, grid, dim3(kFwdBlock), 0, s, ps.e0, ps.e1, 0,
+                          (const T *)xr, (const T *)xc, static_cast<T *>(y),
+                          (const AngleParams *)g.dev, N, S, g.n_ang, g.n_det, g.ds, s0, st,
+                          k, sh);
     return hipGetLastError();
 }
 
@@ -224,63 +261,55 @@ hipError_t back_t(const Geometry &g, int kind, const void *y, void *x, hipStream
 
 namespace {
 std::atomic<int> g_fwd_force_lg{-1};
-}  // namespace
-
-
-// Angles per block of the forward projectors (log2), from measurements on gfx950 (all
-// shapes give the same bits). Four angles per block pay above N = 512 (640^2 x 720
-// angles x 907 bins: 244 us with one angle per block, 177 with four): the 4 MB L2 of
-// an XCD holds only about three band steps of the rows its resident waves read, so rows
-// are reused only by waves walking nearly the same rows at nearly the same time -- the
-// waves of one block at adjacent angles (FP64: 9% faster at 768^2, 27% at 2048^2, 42% at
-// 1536^2; FP32 1-3%). Smaller images stay in L2 anyway; there one angle per block is
-// faster (its rays share each band's cache lines within a wave) unless the last block of
-// each angle leaves more lanes idle than blocks of two angles would (n_det = 363: 512
-// lanes against 384, two angles 6-8% faster).
-int fwd_lg_angles_per_block(const Geometry &g)
-{
-    const int forced = g_fwd_force_lg.load(std::memory_order_relaxed);
-    if (forced >= 0) return forced;
-    if (g.N > 512) return 2;
-    const long long lanes1 = (g.n_det + 255LL) / 256 * 256, lanes2 = (g.n_det + 127LL) / 128 * 128;
-    return lanes2 < lanes1 ? 1 : 0;
-}
-
-void fwd_force_block_shape(int lg_apb) { g_fwd_force_lg.store(lg_apb >= 0 && lg_apb <= 2 ? lg_apb : -1); }
-
-namespace {
 std::atomic<int> g_fwd_stage{-1};
 }  // namespace
-// Eighths of the four-angle forward blocks (line model) that stage their band rows in
-// LDS, from measurements on gfx950 (all shares give the same bits; times per apply at
-// 0 / 2 / 3 eighths): FP32 three eighths (2048^2 x 1800 angles 3.10 / 2.77 / 2.72 ms,
-// 1024^2 x 900 0.45 / 0.41 / 0.41 ms, 640^2 x 720 177 / 166 / 161 us, 256^2 x 360 50 / 43
-// / 42 us, 2048^2 x 600 1.16 / 1.08 / 1.08 ms). FP64, whose gathers return twice the
-// bytes: two eighths at 1024^2 (0.47-0.53 / 0.44-0.47 ms), three below (640^2 x 720 190 /
-// 174 / 175 us, 384^2 x 600 80 / 79 / 74, 256^2 x 360 53 / 52 / 43), where the four
-// angles of a block stay close (N times the angle step at most 4 px; 2048^2 x 600, at
-// 10.7, 1.33-1.37 / 1.41-1.42 ms), and none above 1024 (2048^2 x 1800 3.15-3.23 /
-// 3.10-3.18 / 3.20 ms, within what boxes differ by). The engine's forward items take the
-// FP32 / FP64 rule without the geometry.
-int fwd_stage_eighths(int dtype)
+
+int fwd_stage_share()
 {
-    const int forced = g_fwd_stage.load(std::memory_order_relaxed);
-    if (forced >= 0) return forced;
-    return dtype == ABG_F64 ? 0 : 3;
+    const int share = g_fwd_stage.load(std::memory_order_relaxed);
+    return share >= 0 ? share : 8;
 }
-int fwd_stage_eighths(const Geometry &g, int dtype)
+
+// From measurements on gfx950 (every choice gives the same bits; us per apply, FP64 /
+// FP32; waves = 64-ray groups times angles, fan = N times the angle step in radians, the
+// pixels by which the rays of adjacent angles drift apart across the image):
+//  - Staged in LDS from 2048 waves on (512^2 x 180 angles, 2160 waves: direct 51 / 49, staged
+//    48 / 43; 1024^2 x 180: 156 / 154 and 105 / 92; 512^2 x 720: 107 / 104 and 89 / 73; below,
+//    256^2 x 180, 1080 waves: 22 / 22 and 23 / 22). Blocks whose angles lie too far apart
+//    for one window take the direct walk by themselves.
+//  - Eight angles per block, which halves the copies into LDS of four, once the device holds
+//    two rounds of them (16384 waves) and their windows fit: eight rays drift apart by up to
+//    0.7 x 7 fan, and the window of 128 (FP64) or 256 (FP32) columns spends 102 on the 64 rays
+//    and its margins (fan <= 5 / 30; 2048^2 x 1800: 2300 / 1680 with four, 2050 / 1570 with
+//    eight; 2048^2 x 600, fan 10.7: 940 / 648 and 981 / 604; 1536^2 x 360, 12240 waves: 307 / 254
+//    and 401 / 275).
+//  - Tiles per XCD above N = 896, where the image no longer stays in a 4 MB L2 by itself
+//    (2048^2 x 1800: 2256 / 1760 without, 2100 / 1580 with tiles; 1024^2 x 720: 322 / 265 and
+//    300 / 247; 640^2 x 720, 141 / 110 and 151 / 124, is better without).
+//  - Direct launches (and the other models): one angle per block, or two where that leaves
+//    fewer lanes of the last block idle, up to N = 512; four above.
+// A grid of 2^31 lanes or more stays with the direct kernel, whose grid has two dimensions.
+FwdPlan fwd_plan(const Geometry &g, int dtype)
 {
-    const int forced = g_fwd_stage.load(std::memory_order_relaxed);
-    if (forced >= 0) return forced;
-    if (dtype != ABG_F64) return 3;
-    if (g.N > 1024) return 0;
-    // mean step between listed angles (degrees), in radians
+    const int forced = g_fwd_force_lg.load(std::memory_order_relaxed);
+    const long long groups = (g.n_det + 63LL) / 64, waves = groups * g.n_ang;
+    FwdPlan p{};
+    p.share = fwd_stage_share();
+    p.tiled = g.N > 896;
+    const long long lanes1 = (g.n_det + 255LL) / 256 * 256, lanes2 = (g.n_det + 127LL) / 128 * 128;
+    p.lg = forced >= 0 ? forced : g.N > 512 ? 2 : lanes2 < lanes1 ? 1 : 0;
+    // mean step between listed angles
     const double step = g.n_ang > 1 ? std::fabs(g.theta.back() - g.theta.front()) / (g.n_ang - 1) *
                                           (3.14159265358979323846 / 180.0)
                                     : 1.0;
-    if (g.N * step > 4.0) return 0;
-    return g.N >= 1024 ? 2 : 3;
+    const bool wide = waves >= 16384 && g.N * step <= (dtype == ABG_F64 ? 5.0 : 30.0);
+    if (forced == 2) p.nw = 4;
+    else if (forced < 0 && waves >= 2048) p.nw = wide ? 8 : 4;
+    if (p.share == 0 || waves >= (1LL << 31) / 64) p.nw = 0;
+    return p;
 }
+
+void fwd_force_block_shape(int lg_apb) { g_fwd_force_lg.store(lg_apb >= 0 && lg_apb <= 2 ? lg_apb : -1); }
 void fwd_force_stage_eighths(int e) { g_fwd_stage.store(e >= 0 && e <= 8 ? e : -1); }
 
 size_t fp_workspace_bytes(const Geometry &g, int dtype)

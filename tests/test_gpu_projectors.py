@@ -121,6 +121,39 @@ def test_forward_block_shapes_bit_identical(gpu_lib, kw, dt):
         abg.fp_force_stage_share(-1)
 
 
+# Launches of the staged line-model kernel: four and eight angles per block, plain and tiled
+# block order, with ragged numbers of angles, ray groups and rows, and angles too far apart
+# for one window (those blocks walk directly).
+STAGED_GEOMS = [
+    dict(N=200, n_ang=411, n_det=283),                   # four angles, plain (2055 waves)
+    dict(N=901, n_ang=103, n_det=1279, ang_range=20.0),  # four angles, tiled (2060 waves)
+    dict(N=255, n_ang=2731, n_det=363),                  # eight angles, plain (16386 waves)
+    dict(N=897, n_ang=821, n_det=1273),                  # eight angles, tiled (16420 waves)
+    dict(N=905, n_ang=105, n_det=1217, det_spacing=1.1), # four angles, tiled, wide steps
+]
+
+
+@pytest.mark.parametrize("kw", STAGED_GEOMS, ids=_ids)
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_forward_staged_launches_bit_identical(gpu_lib, kw, dt):
+    """The staged launches write every ray once and give the bits of the direct kernel
+    (one angle per block), which the oracle tests pin."""
+    import torch
+    import paper_2110_01481_amd as abg
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    rng = np.random.default_rng(6)
+    x = torch.tensor(rng.standard_normal(kw["N"] ** 2), dtype=tdt, device="cuda")
+    gg = abg.Geometry(**kw)
+    y = torch.full((gg.m,), float("nan"), dtype=tdt, device="cuda")
+    try:
+        gg.fp(x, out=y)
+        abg.fp_force_block_shape(0)
+        assert torch.equal(gg.fp(x), y)
+    finally:
+        abg.fp_force_block_shape(-1)
+        gg.close()
+
+
 def test_back_projection_of_a_sinogram_over_2gib(gpu_lib):
     """The back projectors read a sinogram of less than 2 GiB through one buffer resource
     with 31-bit offsets, a larger one through clamped 64-bit addresses. A 16^2 image with
