@@ -342,15 +342,16 @@ __device__ inline void back_tile(const T *__restrict__ y, T *__restrict__ x,
 // side for the footprints). A pixel at window coordinate u (bins) takes the bins k with
 // |k - u| below the footprint's reach, at most three:
 //   Joseph^T:  (1/p) max(0, 1 - |k - u| ds / p)           (triangle of half-width p)
-//   strip^T:   (G(e + ds/2) - G(e - ds/2)) / ds, e = |k - u| ds   (see Trapezoid)
+//   strip^T:   the pixel's area over the bin, over ds   (see HalfArea)
 constexpr int kWinV = 40;
 
 template <typename T> struct alignas(16) BackStageV {
     T f, cu, su, su4;     // as BackStage
     T reach;              // footprint half-width in bins
     T js;                 // Joseph: ds / p^2;  strip: ds
-    Trapezoid<T> tz;      // strip: footprint constants; Joseph: invp only
-    T thr;                // B_tau: smallest entry kept
+    T invp;               // 1/p
+    HalfArea<T> half;     // strip: the pixel's footprint on the detector
+    T thr;                // B_tau: smallest entry kept, times ds
 };
 
 template <typename T, int AB = kAngBlock> struct BackLdsV {
@@ -395,8 +396,9 @@ __device__ inline void back_tile_v(const T *__restrict__ y, T *__restrict__ x,
             st.cu = T(Pn.cu);
             st.su = T(Pn.su);
             st.su4 = T(4.0 * Pn.su);
-            st.tz = Trapezoid<T>(Pn, ds);
-            st.thr = T(tau_thr);
+            st.invp = T(Pn.len);
+            st.half = HalfArea<T>(Pn.p, Pn.q);
+            st.thr = T(tau_thr * ds);
             if (KIND == ABG_BP_JOSEPH_T) {
                 st.reach = T(Pn.p / ds);
                 st.js = T(ds * Pn.len * Pn.len);
@@ -433,20 +435,21 @@ __device__ inline void back_tile_v(const T *__restrict__ y, T *__restrict__ x,
     auto tap = [&](const T *win, T u, const BackStageV<T> &P) {
         // window coordinates keep u - reach >= 0.5, so truncation is floor
         const int k0 = (int)(u - P.reach) + 1;
-        const T e0 = fabs(T(k0) - u), e1 = fabs(T(k0 + 1) - u), e2 = fabs(T(k0 + 2) - u);
+        const T e = T(k0) - u;
         T w[3];
         if constexpr (KIND == ABG_BP_JOSEPH_T) {
-            w[0] = fmax(fma(-e0, P.js, P.tz.invp), T(0));
-            w[1] = fmax(fma(-e1, P.js, P.tz.invp), T(0));
-            w[2] = fmax(fma(-e2, P.js, P.tz.invp), T(0));
+            w[0] = fmax(fma(-fabs(e), P.js, P.invp), T(0));
+            w[1] = fmax(fma(-fabs(e + T(1)), P.js, P.invp), T(0));
+            w[2] = fmax(fma(-fabs(e + T(2)), P.js, P.invp), T(0));
         } else {
-            w[0] = P.tz.strip(e0 * P.js);
-            w[1] = P.tz.strip(e1 * P.js);
-            w[2] = P.tz.strip(e2 * P.js);
+            // areas between the bins' edges (times 1/ds, applied to the sum)
+            const T g1 = P.half((e + T(0.5)) * P.js), g2 = P.half((e + T(1.5)) * P.js);
+            w[0] = T(0.5) + g1;
+            w[1] = g2 - g1;
+            w[2] = T(0.5) - g2;
             if constexpr (KIND == ABG_BP_STRIP_TAU) {
-                w[0] = w[0] >= P.thr ? w[0] : T(0);
-                w[1] = w[1] >= P.thr ? w[1] : T(0);
-                w[2] = w[2] >= P.thr ? w[2] : T(0);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) w[i] = w[i] >= P.thr ? w[i] : T(0);
             }
         }
         return fma(w[0], win[k0], fma(w[1], win[k0 + 1], w[2] * win[k0 + 2]));
@@ -477,7 +480,7 @@ __device__ inline void back_tile_v(const T *__restrict__ y, T *__restrict__ x,
             for (int j = 1; j < kPixPerLane; ++j) acc[j] += tap(L.win[t], fma(T(j), P.su4, u0), P);
         }
     }
-    tile_store<T, PAD>(acc, L.part, T(1), x, N, c0, r0, xr, xc, S);
+    tile_store<T, PAD>(acc, L.part, KIND == ABG_BP_JOSEPH_T ? T(1) : T(1.0 / ds), x, N, c0, r0, xr, xc, S);
 }
 
 }  // namespace

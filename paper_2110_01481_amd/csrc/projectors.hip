@@ -10,7 +10,8 @@
 //           of one image row; steep rays read the row-major copy, flat rays a transposed
 //           copy, both zero-padded so that no per-tap bounds test is needed.
 //  back     x = B y (unmatched, linear interpolation on the detector) or x = A^T y,
-//           pixel-driven: a block owns a 16 x 16 tile, each lane 4 of its pixels, and the
+//           pixel-driven. Large images by orbits of four pixels (back_orbit.h), the others
+//           by tiles: a block owns a 16 x 16 tile, each lane 4 of its pixels, and the
 //           eight waves split the angles. For a round of 64 angles the tile's detector
 //           footprint (at most 32 bins per angle) is staged in LDS; every pixel then
 //           reads its two taps per angle from LDS, and the eight wave partials are summed
@@ -22,6 +23,7 @@
 #include <mutex>
 
 #include "back_body.h"
+#include "back_orbit.h"
 #include "fwd_body.h"
 
 namespace abg {
@@ -183,6 +185,38 @@ __global__ __launch_bounds__(kBackThreads, (kBackMinWaves<T, ADJ>)) void back_ke
                                                 x + (size_t)N * S, S);
 }
 
+// Orbits of four pixels (back_orbit.h): 16 x 16 tiles of a quarter of the image, NWV waves
+// splitting the angles; at least four waves per SIMD.
+constexpr int kOrbPix = 4, kOrbAngles = 32;
+template <typename T, int KIND, int NWV, bool PAD>
+__global__ __launch_bounds__(64 * NWV, 4) void back_orbit_kernel(
+    const T *__restrict__ y, T *__restrict__ x, const AngleParams *__restrict__ ang, int N,
+    int n_ang, int n_det, double ds, double s0, double tau_thr, const DevState *st, int k)
+{
+    __shared__ OrbLds<T, KIND, kOrbPix, NWV, kOrbAngles> lds;
+    if (halted(st, k)) return;
+    const int S = N + 2 * kPad;
+    back_orbit_tile<T, KIND, kOrbPix, NWV, kOrbAngles, PAD>(y, x, ang, N, n_ang, n_det, ds, s0,
+                                                            blockIdx.x * 16, blockIdx.y * 16, lds, x,
+                                                            x + (size_t)N * S, S, tau_thr);
+}
+
+// Waves per block of the orbit kernels, or 0 for the tile kernels. An orbit block covers 1024
+// pixels, so a small image leaves CUs without one: the orbits are taken where the blocks
+// spread over the 256 CUs evenly enough for what they save (us per apply, tiles / orbits,
+// interpolating kind in FP32 at 720 angles: 384^2, 56% even, 29 / 32; 512^2, 100%, 43 / 38;
+// 640^2, 78%, 68 / 65; 768^2 x 360, 75%, 44 / 48; 1024^2, 100%, 147 / 123; the three-tap kinds
+// save more: Joseph^T 384^2 66 / 54). One block per CU or less takes 16 waves (512^2 FP64 58 with
+// 8, 51 with 16), more blocks 8. Sinograms of 2 GiB or more take the tiles' 64-bit addresses.
+int back_orbit_waves(const Geometry &g, int kind, size_t elem)
+{
+    constexpr long long kCus = 256;
+    const long long t = ((g.N + 1) / 2 + 15) / 16, b = t * t, rounds = (b + kCus - 1) / kCus;
+    const bool pairs = kind == ABG_BP_HAT || kind == ABG_BP_ADJ;
+    if (!sinogram_fits_offset(g.m(), elem) || 100 * b < (pairs ? 77 : 50) * kCus * rounds) return 0;
+    return b <= kCus ? 16 : 8;
+}
+
 // x == nullptr: the padded copies in ws already hold the input.
 template <typename T>
 hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStream_t s,
@@ -238,6 +272,24 @@ hipError_t back_t(const Geometry &g, int kind, const void *y, void *x, hipStream
     dim3 grid((g.N + kTile - 1) / kTile, (g.N + kTile - 1) / kTile);
     const double s0 = -0.5 * (g.n_det - 1) * g.ds;
     ProfScope ps(kProfBack, s, st ? k : 0, true);
+    const int waves = back_orbit_waves(g, kind, sizeof(T));
+    if (waves) {
+        const int tiles = ((g.N + 1) / 2 + 15) / 16;
+        auto pick = [&](auto nw) {
+            constexpr int NWV = decltype(nw)::value;
+            return kind == ABG_BP_HAT        ? back_orbit_kernel<T, ABG_BP_HAT, NWV, PAD>
+                   : kind == ABG_BP_ADJ      ? back_orbit_kernel<T, ABG_BP_ADJ, NWV, PAD>
+                   : kind == ABG_BP_STRIP_T  ? back_orbit_kernel<T, ABG_BP_STRIP_T, NWV, PAD>
+                   : kind == ABG_BP_JOSEPH_T ? back_orbit_kernel<T, ABG_BP_JOSEPH_T, NWV, PAD>
+                                             : back_orbit_kernel<T, ABG_BP_STRIP_TAU, NWV, PAD>;
+        };
+        auto fn = waves == 16 ? pick(std::integral_constant<int, 16>{}) : pick(std::integral_constant<int, 8>{});
+        hipExtLaunchKernelGGL(fn, dim3(tiles, tiles), dim3(64 * waves), 0, s, ps.e0, ps.e1, 0,
+                              static_cast<const T *>(y), static_cast<T *>(x),
+                              (const AngleParams *)g.dev, g.N, g.n_ang, g.n_det, g.ds, s0, g.tau_thr,
+                              st, k);
+        return hipGetLastError();
+    }
     if (kind == ABG_BP_STRIP_T || kind == ABG_BP_JOSEPH_T || kind == ABG_BP_STRIP_TAU) {
         auto fn = kind == ABG_BP_STRIP_T    ? back_model_kernel<T, ABG_BP_STRIP_T, PAD>
                   : kind == ABG_BP_JOSEPH_T ? back_model_kernel<T, ABG_BP_JOSEPH_T, PAD>

@@ -154,6 +154,52 @@ def test_forward_staged_launches_bit_identical(gpu_lib, kw, dt):
         gg.close()
 
 
+# Back projections over orbits of four pixels: 16 waves (up to 256 blocks) and 8, even and odd
+# images with ragged tiles, angle counts around the 32 of a round, detectors shorter than the
+# image diagonal, both ends of the bin spacings.
+ORBIT_GEOMS = [
+    dict(N=512, n_ang=37, n_det=725),
+    dict(N=449, n_ang=32, n_det=301),
+    dict(N=481, n_ang=7, n_det=600, det_spacing=1.3),
+    dict(N=675, n_ang=33, n_det=957, ang_range=120.0),
+    dict(N=700, n_ang=5, n_det=1325, det_spacing=0.75),
+]
+
+
+@pytest.mark.parametrize("kw", ORBIT_GEOMS, ids=_ids)
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_back_orbits_match_oracle(gpu_lib, kw, dt):
+    import torch
+    go, gg = _pair(kw)
+    tdt, tol = (torch.float64, 1e-12) if dt == "f64" else (torch.float32, 1e-5)
+    y = np.random.default_rng(12).uniform(size=go.m)
+    x = torch.empty(gg.n, dtype=tdt, device="cuda")
+    yt = torch.tensor(y, dtype=tdt, device="cuda")
+    for kind in ("hat", "adj", "strip_t", "joseph_t"):
+        want = go.back(kind)(y)
+        x.fill_(float("nan"))
+        got = gg.bp(yt, kind, out=x).double().cpu().numpy()
+        assert _rel(got, want) <= tol, (kind, _rel(got, want))
+    # B_tau drops whole entries at the threshold, so an entry within rounding of it may fall
+    # either way; y >= 0 and B_tau y falls with tau, which bounds each pixel by thresholds
+    # moved by the entries' rounding (bin positions up to 32, a few units in the last place)
+    gg.set_strip_threshold(0.3)
+    x.fill_(float("nan"))
+    got = gg.bp(yt, "strip_tau", out=x).double().cpu().numpy()
+    delta = 64 * np.finfo(np.float64 if dt == "f64" else np.float32).eps * 4
+    lo, hi = go.B_tau(0.3 + delta)(y), go.B_tau(0.3 - delta)(y)
+    slack = tol * np.abs(hi).max()
+    assert np.all(got >= lo - slack) and np.all(got <= hi + slack)
+    # AB-GMRES takes B's output straight in the forward projector's copies: one step gives
+    # x_1 = (<b, A B b> / ||A B b||^2) B b
+    import paper_2110_01481_amd as abg
+    r = abg.gmres("ab", gg, yt, 1)
+    bb = gg.bp(yt)
+    q = gg.fp(bb)
+    want = (torch.dot(yt.double(), q.double()) / torch.dot(q.double(), q.double()) * bb.double()).cpu().numpy()
+    assert _rel(r.x.double().cpu().numpy(), want) <= tol
+
+
 def test_back_projection_of_a_sinogram_over_2gib(gpu_lib):
     """The back projectors read a sinogram of less than 2 GiB through one buffer resource
     with 31-bit offsets, a larger one through clamped 64-bit addresses. A 16^2 image with
