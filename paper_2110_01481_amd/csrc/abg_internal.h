@@ -214,10 +214,10 @@ void fwd_force_block_shape(int lg_apb);
 // How a geometry's forward projection is launched (the choice single solves make, with
 // the forced settings applied).
 struct FwdPlan {
-    int nw;      // line model: waves (angles) per block of the staged kernel; 0: direct kernel
+    int nw;      // line and Joseph models: waves (angles) per block of the staged kernel; 0: direct
     int share;   // eighths of the staged kernel's blocks that stage (8: all)
     bool tiled;  // staged kernel: blocks dealt out in tiles, one XCD each
-    int lg;      // direct and model kernels: log2 of the angles per block of 256 threads
+    int lg;      // direct kernel: log2 of the angles per block of 256 threads
 };
 FwdPlan fwd_plan(const Geometry &g, int dtype);
 // Eighths of staged blocks that stage: the forced share, or all.

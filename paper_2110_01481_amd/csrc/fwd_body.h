@@ -1,6 +1,6 @@
-// Device code of the ray-driven forward projector (line model), shared by the
-// single-problem kernels (projectors.hip) and the batched kernels (batch.hip), so that
-// both run the same arithmetic.
+// Device code of the ray-driven forward projectors, shared by the single-problem kernels
+// (projectors.hip) and the batched kernels (batch.hip, line model), so that both run the same
+// arithmetic.
 #pragma once
 
 #include <cmath>
@@ -82,13 +82,56 @@ constexpr int kChunk = 8;
 // band step is an add with carry, the pixel index is the integer part and the fraction
 // gives the weight.
 template <typename T> struct Band;
-// Share of a band segment that lies left of the pixel edge it crosses: the segment is 1/p
-// long and the part left of the edge (1 - frac) / q, so the share is
-// min(1, (1 - frac) p/q). One multiply-add with the output clamped to [0, 1]; the length
-// 1/p is a common factor of the whole ray.
-template <typename T> struct BandWeights {
+// What the taps of a band weigh, as shares of the band's total 1/p (a common factor of the
+// whole ray), and where a walk's position sits in band 0 (pixels from the image edge, the
+// ray's minor-axis coordinate there being u0 and moving by m per band).
+//
+// Line: the position is the segment's lower end; it is 1/p long and the part left of the
+// pixel edge it crosses (1 - frac) / q, so that share is min(1, (1 - frac) p/q): one
+// multiply-add with the output clamped to [0, 1].
+// Joseph: the pixels around the crossing point of the band's centre line (pixel-centre
+// coordinates) share 1 - frac and frac.
+// Strip: the strip of width ds cuts a parallelogram out of the band, whose extent along the
+// band is a trapezoid (boxes of ds/p and |m| convolved); the shares of the four pixels from its
+// lower end on (it is at most three long for ds <= 1.4) are differences of its half area at
+// the three edges between them: about 40 vector instructions per band, which bound it, where
+// two antiderivatives per pixel took 133 (512^2 x 720: FP64 1120 -> 306 us, FP32 560 -> 177).
+template <typename T, int MODEL> struct BandWeights;
+template <typename T> struct BandWeights<T, ABG_FP_LINE> {
     T pq;
-    __device__ explicit BandWeights(double pq_) : pq(T(pq_)) {}
+    __device__ BandWeights(const AngleParams &P, double) : pq(T(P.pq)) {}
+    __device__ static double first(const AngleParams &P, double, double u0) { return u0 + fmin(P.m, 0.0); }
+};
+template <typename T> struct BandWeights<T, ABG_FP_JOSEPH> {
+    __device__ BandWeights(const AngleParams &, double) {}
+    __device__ static double first(const AngleParams &P, double, double u0)
+    {
+        return fma(0.5, P.m, u0) - 0.5;
+    }
+};
+template <typename T> struct BandWeights<T, ABG_FP_STRIP> {
+    HalfArea<T> half;
+    T e1, e2, e3;           // the edges from the trapezoid's centre at fraction 0
+    __device__ BandWeights(const AngleParams &P, double ds)
+        : half(fmax(ds * P.len, fabs(P.m)), fmin(ds * P.len, fabs(P.m)))
+    {
+        const double h = 0.5 * (ds * P.len + fabs(P.m));
+        e1 = T(1.0 - h);
+        e2 = T(2.0 - h);
+        e3 = T(3.0 - h);
+    }
+    __device__ static double first(const AngleParams &P, double ds, double u0)
+    {
+        return fma(0.5, P.m, u0) - 0.5 * (ds * P.len + fabs(P.m));
+    }
+    __device__ void shares(T f, T (&w)[4]) const
+    {
+        const T g1 = half(e1 - f), g2 = half(e2 - f), g3 = half(e3 - f);
+        w[0] = T(0.5) + g1;
+        w[1] = g2 - g1;
+        w[2] = g3 - g2;
+        w[3] = T(0.5) - g3;
+    }
 };
 
 // Sum of a ray's taps. FP32: the bands of a group are summed in FP32 and the groups in FP64.
@@ -115,16 +158,12 @@ template <typename T> struct RaySum {
 
 template <> struct Band<double> {
     double lo0, m, lo;
-    // lo0_: lower minor-axis edge of band 0, in pixels from the image edge; floor(lo) is
-    // the padded column itself
+    // lo0_: position in band 0, in pixels from the image edge; floor(lo) is the padded
+    // column itself
     __device__ Band(double lo0_, double m_) : lo0(lo0_ + kPad), m(m_), lo(lo0) {}
     __device__ void seek(int r) { lo = fma((double)r, m, lo0); }
     __device__ void rebase(int r) { seek(r); }
     __device__ void next() { lo += m; }
-    __device__ unsigned column(unsigned cmax) const
-    {
-        return min((unsigned)(int)floor(lo), cmax);
-    }
     // padded column, unclamped, by truncation. A wave walks only bands near those some
     // lane's ray crosses (at most N of them, |m| <= 1), and the lanes of a wave lie within
     // 63 bins of each other (63 * 64 * sqrt(2) < 5702 px for the spacings a geometry
@@ -134,17 +173,16 @@ template <> struct Band<double> {
     // truncation is floor; below, truncation lands in the zero padding (lo > -1) or before
     // the row (out of range, read as zero) as floor would.
     __device__ int column_raw() const { return (int)lo; }
-    // share of the band segment left of the pixel edge at floor(lo) + 1, from the
-    // fractional part of lo (exactly lo - floor(lo) for lo >= 0). p/q is the same in every
-    // lane (a wave walks one angle), so a scalar operand holds it.
-    __device__ double left_share(const BandWeights<double> &b) const
+    // fractional part of lo (exactly lo - floor(lo) for lo >= 0)
+    __device__ double frac() const { return __builtin_amdgcn_fract(lo); }
+    // p/q is the same in every lane (a wave walks one angle): a scalar operand holds it
+    __device__ double left_share(const BandWeights<double, ABG_FP_LINE> &b) const
     {
         double w;
-        asm("v_fma_f64 %0, -%1, %2, %2 clamp" : "=v"(w) : "v"(__builtin_amdgcn_fract(lo)), "s"(b.pq));
+        asm("v_fma_f64 %0, -%1, %2, %2 clamp" : "=v"(w) : "v"(frac()), "s"(b.pq));
         return w;
     }
-    // (lo - floor(lo)) * s
-    __device__ double frac_scaled(double s) const { return (lo - floor(lo)) * s; }
+    __device__ double left_share(const BandWeights<double, ABG_FP_JOSEPH> &) const { return 1.0 - frac(); }
 };
 
 template <> struct Band<float> {
@@ -177,36 +215,27 @@ template <> struct Band<float> {
         c += mi + (nf < f ? 1 : 0);
         f = nf;
     }
-    __device__ unsigned column(unsigned cmax) const
-    {
-        return (unsigned)min(max(c, 0), (int)cmax);
-    }
     __device__ int column_raw() const { return c; }
-    __device__ float left_share(const BandWeights<float> &b) const
+    __device__ float frac() const { return (float)f * 0x1p-32f; }
+    __device__ float left_share(const BandWeights<float, ABG_FP_LINE> &b) const
     {
         return __builtin_amdgcn_fmed3f(fmaf((float)f, -b.pq * 0x1p-32f, b.pq), 0.f, 1.f);
     }
-    // fractional part times s * 2^32 (the caller folds 2^-32 into s)
-    __device__ float frac_scaled(float s) const { return (float)f * s; }
+    __device__ float left_share(const BandWeights<float, ABG_FP_JOSEPH> &) const
+    {
+        return fmaf((float)f, -0x1p-32f, 1.f);
+    }
 };
 
-// The two adjacent pixels a band segment can touch, fetched with one load from a
-// wave-uniform row pointer plus a 32-bit byte offset (one wide gather is cheaper for
-// the texture address unit than two narrow ones).
+// Two adjacent pixels of a row, fetched with one load (one wide gather is cheaper for the
+// texture address unit than two narrow ones).
 template <typename T> struct alignas(sizeof(T)) Taps {
     T a, b;
 };
-template <typename T>
-__device__ inline Taps<T> load_taps(const T *row, unsigned col)
-{
-    const unsigned boff = col * (unsigned)sizeof(T);
-    return *reinterpret_cast<const Taps<T> *>(reinterpret_cast<const char *>(row) + boff);
-}
-
-// The same two taps through a buffer resource spanning exactly one padded row of S
-// elements: the hardware range check returns zero for a column outside the row (a lane
-// walking bands outside its own chord, negative columns included, as their unsigned byte
-// offset is huge), so the walk needs no clamp.
+// A buffer resource spans exactly one padded row of S elements: the hardware range check
+// returns zero for a column outside the row (a lane walking bands outside its own chord,
+// negative columns included, as their unsigned byte offset is huge), so the walk needs no
+// clamp.
 template <typename T>
 __device__ inline Taps<T> load_taps_row(const T *row, int S, int col)
 {
@@ -219,135 +248,6 @@ __device__ inline Taps<T> load_taps_row(const T *row, int S, int col)
         return __builtin_bit_cast(Taps<T>, __builtin_amdgcn_raw_buffer_load_b128(r, boff, 0, 0));
     }
 }
-
-// Ray i of angle a (i may exceed n_det: such lanes only take part in the wave's band
-// range and store nothing). Called by whole waves of consecutive rays.
-//
-// A group of bands per trip, their loads issued before their use: this walk serves
-// launches of few waves and, among staged blocks, those whose angles lie far apart, which
-// both wait on the gather latency (512^2 x 60 angles: 87 us with two bands per trip, 40 with
-// eight; a launch that fills the device many times over is better off with two, 3.2 against
-// 3.9 ms at 2048^2 x 1800 in FP64, but it stages its rows).
-template <typename T>
-__device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict__ xc,
-                                   T *__restrict__ y, const AngleParams *__restrict__ ang, int a,
-                                   int i, int N, int S, int n_det, double ds, double s0)
-{
-    const AngleParams P = ang[a];
-    const T *img = (P.steep ? xr : xc) + kPad;
-    const double half = 0.5 * N;
-    const double si = s0 + (double)i * ds;
-    // minor-axis coordinate, in pixels from the image edge, where the ray enters band 0
-    const double u0 = fma(si, P.inv, fma(-half, P.m, half));
-    const double lo_clamp = -(double)kPad, hi_clamp = (double)(N + kPad - 2);
-    T acc = T(0);
-
-    if (P.axis) {
-        // The ray stays in one column (or row) of pixels; on a pixel edge it is split
-        // evenly between the two pixels that share the edge.
-        const double uc = fmin(fmax(u0, lo_clamp), hi_clamp);
-        const double nearest = rint(uc);
-        int c0;
-        T w0, w1;
-        if (fabs(uc - nearest) <= kEdgeTie) {
-            c0 = (int)nearest - 1;
-            w0 = w1 = T(0.5 * P.len);
-        } else {
-            c0 = (int)floor(uc);
-            w0 = T(P.len);
-            w1 = T(0);
-        }
-        if (u0 < lo_clamp || u0 > hi_clamp) c0 = -kPad;   // outside: read zero padding
-        c0 = min(max(c0, -kPad), N + kPad - 2);           // both taps inside the padded row
-        // a group of rows per trip, their loads issued before their use (one row at a time,
-        // the few axis-parallel angles would outlast the rest of a launch); rows past the
-        // image read as zero
-        const T *row = img - kPad;
-        RaySum<T> sum;
-        for (int r = 0; r < N; r += kChunk) {
-            Taps<T> t[kChunk];
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j)
-                t[j] = load_taps_row(row + (size_t)j * S, r + j < N ? S : 0, c0 + kPad);
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                sum.tap(w0, t[j].a);
-                sum.tap(w1, t[j].b);
-            }
-            sum.group_done();
-            row += kChunk * (size_t)S;
-        }
-        acc = sum.times(1.0);                          // w0, w1 hold the length
-    } else {
-        // Band r holds the minor-axis interval [lo_r, lo_r + |m|], lo_r = lo0 + r*m.
-        const double lo0 = u0 + fmin(P.m, 0.0);
-        const double am = fabs(P.m);
-        double ra, rb;
-        if (P.m > 0.0) {
-            ra = (-1.0 - am - lo0) / am;
-            rb = (N + 1.0 - lo0) / am;
-        } else {
-            ra = (lo0 - (N + 1.0)) / am;
-            rb = (lo0 + 1.0 + am) / am;
-        }
-        ra = fmin(fmax(ra, 0.0), (double)N);
-        rb = fmin(fmax(rb, 0.0), (double)N);
-        int r0 = (int)floor(ra);
-        int r1 = min((int)ceil(rb) + 1, N);
-        if (i >= n_det) {
-            r0 = N;
-            r1 = 0;
-        }
-        // wave-uniform band range, from a multiple of kChunk: lanes outside their own chord
-        // read zero padding
-        const int wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0)) & ~(kChunk - 1);
-        const int wr1 = __builtin_amdgcn_readfirstlane(wave_max_i(r1));
-        Band<T> band(lo0, P.m);
-        band.seek(wr0);
-        // row-start pointer (padding included); taps outside the padded row read zero
-        const T *row = img - kPad + (size_t)wr0 * S;
-        const BandWeights<T> bw(P.pq);
-        RaySum<T> sum;
-        for (int r = wr0; r < wr1; r += kChunk) {
-            int c[kChunk];
-            T w[kChunk], v0[kChunk], v1[kChunk];
-            band.rebase(r);
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                c[j] = band.column_raw();
-                w[j] = band.left_share(bw);
-                band.next();
-            }
-            // bands past the image read as zero
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                const Taps<T> t = load_taps_row(row + (size_t)j * S, r + j < N ? S : 0, c[j]);
-                v0[j] = t.a;
-                v1[j] = t.b;
-            }
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                sum.tap(w[j], v0[j]);
-                sum.tap(T(1) - w[j], v1[j]);
-            }
-            sum.group_done();
-            row += kChunk * (size_t)S;
-        }
-        acc = sum.times(P.len);
-    }
-    if (i < n_det) y[(size_t)a * n_det + i] = acc;
-}
-
-// ---- strip and interpolation (Joseph) models -----------------------------------------
-// Both walk the bands of the line model. Joseph samples each band on its centre line:
-// the ray crosses it at minor coordinate u* = u0 + (r + 1/2) m, and with b = u* - 1/2
-// (pixel-centre coordinates) the pixels floor(b) and floor(b) + 1 get (1 - frac b)/p and
-// (frac b)/p. The strip model (a strip of width ds around the ray; area of strip and
-// pixel over ds) weighs every pixel of the band whose centre lies within R pixels of b,
-// R = ((p + q)/2 + ds/2)/p, by the line-model trapezoid integrated over the strip: with
-// e = |b - c| p the centre's distance from the ray in detector units,
-//     w = (G(e + ds/2) - G(e - ds/2)) / ds,   G = antiderivative of the trapezoid.
-// For ds <= 1.4 that is at most four consecutive pixels, fetched with one 16-byte load.
 
 // Bands [r0, r1) whose minor-axis interval, widened by `extra` pixels on both sides, can
 // meet [-1, N + 1]; empty for rays that store nothing.
@@ -369,162 +269,160 @@ __device__ inline void band_range(double lo0, double m, int N, double extra, boo
     r1 = live ? min((int)ceil(rb) + 1, N) : 0;
 }
 
-template <typename T> struct alignas(sizeof(T)) Quad {
-    T v[4];
-};
-
-// Joseph's model, ray i of angle a (called by whole waves of consecutive rays).
+// Four adjacent pixels of a row, columns col .. col + 3. A column outside the row is zero; where
+// the four straddle an end of the row, those inside it are padding (kPad = 4), zero as well.
 template <typename T>
-__device__ inline void forward_ray_joseph(const T *__restrict__ xr, const T *__restrict__ xc,
-                                          T *__restrict__ y, const AngleParams *__restrict__ ang,
-                                          int a, int i, int N, int S, int n_det, double ds,
-                                          double s0)
+__device__ inline void load_quad_row(const T *row, int S, int col, Taps<T> (&t)[2])
 {
-    const AngleParams P = ang[a];
-    const T *img = (P.steep ? xr : xc) + kPad;
-    const double half = 0.5 * N;
-    const double si = s0 + (double)i * ds;
-    const double u0 = fma(si, P.inv, fma(-half, P.m, half));
-    T acc = T(0);
-    if (P.axis) {
-        // u* is the same in every band; out of reach, both taps read zero padding
-        const double b = fmin(fmax(u0 - 0.5, -(double)kPad), (double)(N + kPad - 2));
-        const int c0 = (int)floor(b);
-        const T w1 = T((b - c0) * P.len), w0 = T(P.len) - w1;
-        const T *p = img + c0;
-        for (int r = 0; r < N; ++r) {
-            acc = fma(w0, p[0], acc);
-            acc = fma(w1, p[1], acc);
-            p += S;
-        }
+    if constexpr (sizeof(T) == 4) {
+        struct Q {
+            Taps<T> t[2];
+        };
+        __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T *>(row), (short)0, S * (int)sizeof(T), kRawBufferFlags);
+        const Q q = __builtin_bit_cast(Q, __builtin_amdgcn_raw_buffer_load_b128(r, col * (int)sizeof(T), 0, 0));
+        t[0] = q.t[0];
+        t[1] = q.t[1];
     } else {
-        const double lo0 = u0 + fmin(P.m, 0.0);
-        int r0, r1;
-        band_range(lo0, P.m, N, 0.0, i < n_det, r0, r1);
-        const int wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0));
-        const int wr1 = __builtin_amdgcn_readfirstlane(wave_max_i(r1));
-        // b at band wr0
-        Band<T> band(fma((double)wr0 + 0.5, P.m, u0) - 0.5, P.m);
-        const T *row = img - kPad + (size_t)wr0 * S;
-        const T len = T(P.len);
-        const T fs = sizeof(T) == 4 ? T(P.len * 0x1p-32) : len;
-        const unsigned cmax = (unsigned)(N + 2 * kPad - 2);
-        int r = wr0;
-        for (; r + 4 <= wr1; r += 4) {
-            unsigned c[4];
-            T w[4], v0[4], v1[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                c[j] = band.column(cmax);
-                w[j] = band.frac_scaled(fs);
-                band.next();
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const Taps<T> t = load_taps(row + (size_t)j * S, c[j]);
-                v0[j] = t.a;
-                v1[j] = t.b;
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                acc = fma(len - w[j], v0[j], acc);
-                acc = fma(w[j], v1[j], acc);
-            }
-            row += 4 * (size_t)S;
-        }
-        for (; r < wr1; ++r) {
-            const unsigned c = band.column(cmax);
-            const T w = band.frac_scaled(fs);
-            band.next();
-            const Taps<T> t = load_taps(row, c);
-            acc = fma(len - w, t.a, acc);
-            acc = fma(w, t.b, acc);
-            row += S;
-        }
+        t[0] = load_taps_row(row, S, col);
+        t[1] = load_taps_row(row, S, col + 2);
     }
-    if (i < n_det) y[(size_t)a * n_det + i] = acc;
 }
 
-// Strip model, ray i of angle a (called by whole waves of consecutive rays; ds <= 1.4).
-template <typename T>
-__device__ inline void forward_ray_strip(const T *__restrict__ xr, const T *__restrict__ xc,
-                                         T *__restrict__ y, const AngleParams *__restrict__ ang,
-                                         int a, int i, int N, int S, int n_det, double ds,
-                                         double s0)
+// Ray i of angle a (i may exceed n_det: such lanes only take part in the wave's band
+// range and store nothing). Called by whole waves of consecutive rays.
+//
+// A group of bands per trip, their loads issued before their use: this walk serves
+// launches of few waves and, among staged blocks, those whose angles lie far apart, which
+// both wait on the gather latency (512^2 x 60 angles: 87 us with two bands per trip, 40 with
+// eight; a launch that fills the device many times over is better off with two, 3.2 against
+// 3.9 ms at 2048^2 x 1800 in FP64, but it stages its rows).
+// bands' weights and positions: BandWeights.
+template <typename T, int MODEL = ABG_FP_LINE>
+__device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict__ xc,
+                                   T *__restrict__ y, const AngleParams *__restrict__ ang, int a,
+                                   int i, int N, int S, int n_det, double ds, double s0)
 {
     const AngleParams P = ang[a];
-    const T *img = P.steep ? xr : xc;   // row starts, padding included
+    const T *img = P.steep ? xr : xc;                  // row starts, padding included
     const double half = 0.5 * N;
     const double si = s0 + (double)i * ds;
+    // minor-axis coordinate, in pixels from the image edge, where the ray enters band 0
     const double u0 = fma(si, P.inv, fma(-half, P.m, half));
-    const double R = (P.half + 0.5 * ds) * P.len;     // reach in pixels
-    const Trapezoid<T> tz(P, ds);
-    const T pT = T(P.p);
-    // pixel c0 + k of a band, with c0 = floor(b - R) + 1 and f = frac(b - R + 1), lies
-    // b - c0 - k = f + (R - 1 - k) from the crossing point
-    const T d0 = T(R - 1.0);
-    const unsigned cmax = (unsigned)(S - 4);           // the four pixels stay in the row
-    T acc = T(0);
-    auto band4 = [&](T f, const Quad<T> &v) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const T e = fabs(f + (d0 - T(k))) * pT;
-            acc = fma(tz.strip(e), v.v[k], acc);
+    RaySum<T> sum;
+
+    if (P.axis && MODEL != ABG_FP_STRIP) {
+        // The ray stays in one column (or row) of pixels; on a pixel edge a line is split
+        // evenly between the two pixels that share the edge. A group of rows per trip, their
+        // loads issued before their use (one row at a time, the few axis-parallel angles
+        // would outlast the rest of a launch); rows past the image read as zero.
+        const double lo_clamp = -(double)kPad, hi_clamp = (double)(N + kPad - 2);
+        const double uc = fmin(fmax(MODEL == ABG_FP_JOSEPH ? u0 - 0.5 : u0, lo_clamp), hi_clamp);
+        const double nearest = rint(uc);
+        int c0 = (int)floor(uc);
+        T w0 = T(1), w1 = T(0);
+        if (MODEL == ABG_FP_JOSEPH) {
+            w1 = T(uc - c0);
+            w0 = T(1) - w1;
+        } else if (fabs(uc - nearest) <= kEdgeTie) {
+            c0 = (int)nearest - 1;
+            w0 = w1 = T(0.5);
         }
-    };
-    if (P.axis) {
-        // first pixel (padded index) and f, clamped into the row: out of reach only
-        // padding is read
-        const double pb = fmin(fmax(u0 - 0.5 - R + 1.0 + kPad, 0.0), (double)(N + 2 * kPad - 4));
-        const int c0 = (int)floor(pb);
-        const T f = T(pb - c0);
-        const T *p = img + c0;
-        for (int r = 0; r < N; ++r) {
-            const Quad<T> v = *reinterpret_cast<const Quad<T> *>(p);
-            band4(f, v);
-            p += S;
+        if (u0 < lo_clamp || u0 > hi_clamp) c0 = -kPad;   // outside: read zero padding
+        c0 = min(max(c0, -kPad), N + kPad - 2);           // both taps inside the padded row
+        const T *row = img;
+        for (int r = 0; r < N; r += kChunk) {
+            Taps<T> t[kChunk];
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j)
+                t[j] = load_taps_row(row + (size_t)j * S, r + j < N ? S : 0, c0 + kPad);
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j) {
+                sum.tap(w0, t[j].a);
+                sum.tap(w1, t[j].b);
+            }
+            sum.group_done();
+            row += kChunk * (size_t)S;
         }
     } else {
-        const double lo0 = u0 + fmin(P.m, 0.0);
+        using BW = BandWeights<T, MODEL>;
+        const double lo0 = BW::first(P, ds, u0);
+        const double reach = MODEL == ABG_FP_STRIP ? 0.5 * ds * P.len : 0.0;
         int r0, r1;
-        band_range(lo0, P.m, N, R, i < n_det, r0, r1);
-        const int wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0));
+        if (MODEL == ABG_FP_STRIP && P.axis) {
+            // the same columns in every band (at most four from lo0 on)
+            const bool live = i < n_det && lo0 > -4.0 && lo0 < N;
+            r0 = live ? 0 : N;
+            r1 = live ? N : 0;
+        } else {
+            band_range(u0 + fmin(P.m, 0.0), P.m, N, reach, i < n_det, r0, r1);
+        }
+        // wave-uniform band range, from a multiple of kChunk: lanes outside their own chord
+        // read zero padding
+        const int wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0)) & ~(kChunk - 1);
         const int wr1 = __builtin_amdgcn_readfirstlane(wave_max_i(r1));
-        // b - R + 1 at band wr0
-        Band<T> band(fma((double)wr0 + 0.5, P.m, u0) - 0.5 - R + 1.0, P.m);
+        Band<T> band(lo0, P.m);
+        band.seek(wr0);
+        // row-start pointer; taps outside the padded row read zero
         const T *row = img + (size_t)wr0 * S;
-        const T fs = sizeof(T) == 4 ? T(0x1p-32) : T(1);
-        int r = wr0;
-        for (; r + 2 <= wr1; r += 2) {
-            unsigned c[2];
-            T f[2];
-            Quad<T> v[2];
+        const BW bw(P, ds);
+        for (int r = wr0; r < wr1; r += kChunk) {
+            band.rebase(r);
+            if constexpr (MODEL == ABG_FP_STRIP) {
+                // FP64 taps take eight registers a band: two trips per group
+                constexpr int kTrip = sizeof(T) == 8 ? kChunk / 2 : kChunk;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                c[j] = band.column(cmax);
-                f[j] = band.frac_scaled(fs);
-                band.next();
+                for (int j0 = 0; j0 < kChunk; j0 += kTrip) {
+                    T f[kTrip];
+                    Taps<T> t[kTrip][2];
+#pragma unroll
+                    for (int j = 0; j < kTrip; ++j) {
+                        const int b = j0 + j, c = band.column_raw();
+                        f[j] = band.frac();
+                        band.next();
+                        load_quad_row(row + (size_t)b * S, r + b < N ? S : 0, c, t[j]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < kTrip; ++j) {
+                        T w[4];
+                        bw.shares(f[j], w);
+                        sum.tap(w[0], t[j][0].a);
+                        sum.tap(w[1], t[j][0].b);
+                        sum.tap(w[2], t[j][1].a);
+                        sum.tap(w[3], t[j][1].b);
+                    }
+                    if (kTrip < kChunk) asm volatile("" ::: "memory");
+                }
+            } else {
+                int c[kChunk];
+                T w[kChunk], v0[kChunk], v1[kChunk];
+#pragma unroll
+                for (int j = 0; j < kChunk; ++j) {
+                    c[j] = band.column_raw();
+                    w[j] = band.left_share(bw);
+                    band.next();
+                }
+                // bands past the image read as zero
+#pragma unroll
+                for (int j = 0; j < kChunk; ++j) {
+                    const Taps<T> t = load_taps_row(row + (size_t)j * S, r + j < N ? S : 0, c[j]);
+                    v0[j] = t.a;
+                    v1[j] = t.b;
+                }
+#pragma unroll
+                for (int j = 0; j < kChunk; ++j) {
+                    sum.tap(w[j], v0[j]);
+                    sum.tap(T(1) - w[j], v1[j]);
+                }
             }
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                v[j] = *reinterpret_cast<const Quad<T> *>(reinterpret_cast<const char *>(
-                    row + (size_t)j * S) + c[j] * (unsigned)sizeof(T));
-#pragma unroll
-            for (int j = 0; j < 2; ++j) band4(f[j], v[j]);
-            row += 2 * (size_t)S;
-        }
-        if (r < wr1) {
-            const unsigned c = band.column(cmax);
-            const T f = band.frac_scaled(fs);
-            const Quad<T> v = *reinterpret_cast<const Quad<T> *>(
-                reinterpret_cast<const char *>(row) + c * (unsigned)sizeof(T));
-            band4(f, v);
+            sum.group_done();
+            row += kChunk * (size_t)S;
         }
     }
-    if (i < n_det) y[(size_t)a * n_det + i] = acc;
+    if (i < n_det) y[(size_t)a * n_det + i] = sum.times(P.len);
 }
 
-// ---- line model, four angles per block, band rows staged in LDS -------------------------
+// ---- several angles per block, band rows staged in LDS (line and Joseph models) -----------
 // The forward walk above issues one 64-lane gather per band and wave, and the texture
 // path takes them at four lane addresses per cycle: that rate bounds it. A block of four
 // adjacent angles (one wave each) and the same 64 rays reads nearly the same columns of
@@ -569,7 +467,7 @@ __device__ inline long long uniform_ll(long long v)
 // Angles a0 .. a0 + 3 (wave w takes a0 + w), rays ray0 .. ray0 + 63 of each. All four
 // waves call it (also for angles past n_ang); it starts with a block-wide barrier, so
 // that consecutive calls of a block may share L.
-template <typename T, int NW>
+template <typename T, int NW, int MODEL = ABG_FP_LINE>
 __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *__restrict__ xc,
                                             T *__restrict__ y, const AngleParams *__restrict__ ang,
                                             int a0, int ray0, int N, int S, int n_ang, int n_det,
@@ -590,9 +488,9 @@ __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *_
             const double half = 0.5 * N;
             const double si = s0 + (double)i * ds;
             const double u0 = fma(si, P.inv, fma(-half, P.m, half));
-            lo0 = u0 + fmin(P.m, 0.0);
+            lo0 = BandWeights<T, MODEL>::first(P, ds, u0);
             int r0, r1;
-            band_range(lo0, P.m, N, 0.0, i < n_det, r0, r1);
+            band_range(u0 + fmin(P.m, 0.0), P.m, N, 0.0, i < n_det, r0, r1);
             wr0 = __builtin_amdgcn_readfirstlane(wave_min_i(r0)) & ~(kChunk - 1);
             wr1 = __builtin_amdgcn_readfirstlane(wave_max_i(r1));
             const double l0 = lane_value_f64(lo0, 0), l63 = lane_value_f64(lo0, 63);
@@ -641,7 +539,7 @@ __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *_
         staged = fmax(hb - lb, he - le) + (kChunk - 1) * fabs(slope) + 6.0 <= (double)W;
     }
     if (!staged) {
-        if (a < n_ang) forward_ray(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
+        if (a < n_ang) forward_ray<T, MODEL>(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
         return;
     }
     T acc = T(0);
@@ -667,7 +565,7 @@ __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *_
         using LdsT = __attribute__((address_space(3))) const T;
         using LdsC = __attribute__((address_space(3))) const char;
         Band<T> band(lo0, P.m);
-        const BandWeights<T> bw(P.pq);
+        const BandWeights<T, MODEL> bw(P, ds);
         RaySum<T> sum;
         int org = (int)(ofx >> 32);
         stage(rb0, 0, org);

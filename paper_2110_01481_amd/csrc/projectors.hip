@@ -64,19 +64,6 @@ struct FwdShape {
     }
 };
 
-template <typename T>
-__global__ __launch_bounds__(kFwdBlock) void forward_kernel(
-    const T *__restrict__ xr, const T *__restrict__ xc, T *__restrict__ y,
-    const AngleParams *__restrict__ ang, int N, int S, int n_ang, int n_det, double ds,
-    double s0, const DevState *st, int k, FwdShape sh)
-{
-    if (halted(st, k)) return;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int a = sh.wave_angle(wave);
-    if (a >= n_ang) return;
-    forward_ray(xr, xc, y, ang, a, sh.lane_ray(wave), N, S, n_det, ds, s0);
-}
-
 // Order of the blocks of a staged launch: ngx ray groups (64 rays) by ngy angle groups (NW
 // angles). With rows == 0 the ray group runs fastest. Otherwise the blocks come in tiles of
 // one ray group by `rows` angle groups, dealt out to the eight XCDs (blocks b with equal b
@@ -103,14 +90,15 @@ struct FwdOrder {
 };
 constexpr int kFwdTileRows = 4;
 
-// Line model, NW angles per block, band rows staged in LDS (forward_block_staged): bound by
+// Line and Joseph models, NW angles per block, band rows staged in LDS
+// (forward_block_staged): bound by
 // the VALU (8 instructions per band, wave and ray; 83% busy at 2048^2 x 1800 in FP64) beside
 // 8 cycles of LDS reads per band and wave. 2048^2 x 1800 x 2897: FP64 3.20 -> 2.07 ms, FP32
 // 2.77 -> 1.58 ms against the direct walk with the staged share it had; L2 fills 15.4 -> 5.0 GB
 // (FP64), gathers 1.1e8 -> 1.6e7 per launch. A share
 // of the blocks below eight eighths (tests and measurements; spread over the grid by a hash
 // of the block) stages, the others take their taps straight from the image copies.
-template <typename T, int NW>
+template <typename T, int NW, int MODEL>
 __global__ __launch_bounds__(64 * NW) void forward_staged_kernel(
     const T *__restrict__ xr, const T *__restrict__ xc, T *__restrict__ y,
     const AngleParams *__restrict__ ang, int N, int S, int n_ang, int n_det, double ds,
@@ -122,19 +110,19 @@ __global__ __launch_bounds__(64 * NW) void forward_staged_kernel(
     if (!ord.block(blockIdx.x, gx, gy)) return;
     const unsigned b = (unsigned)(gy * ord.ngx + gx);
     if ((int)((b * 0x9E3779B1u) >> 29) < stage_eighths) {
-        forward_block_staged<T, NW>(xr, xc, y, ang, gy * NW, gx * 64, N, S, n_ang, n_det, ds, s0,
-                                    lds);
+        forward_block_staged<T, NW, MODEL>(xr, xc, y, ang, gy * NW, gx * 64, N, S, n_ang, n_det, ds,
+                                           s0, lds);
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int a = gy * NW + wave;
     if (a >= n_ang) return;
-    forward_ray(xr, xc, y, ang, a, gx * 64 + ((int)threadIdx.x & 63), N, S, n_det, ds, s0);
+    forward_ray<T, MODEL>(xr, xc, y, ang, a, gx * 64 + ((int)threadIdx.x & 63), N, S, n_det, ds, s0);
 }
 
-// Strip (MODEL = ABG_FP_STRIP) and interpolation (ABG_FP_JOSEPH) models.
+// Every ray by itself, MODEL = ABG_FP_LINE, ABG_FP_STRIP or ABG_FP_JOSEPH.
 template <typename T, int MODEL>
-__global__ __launch_bounds__(kFwdBlock) void forward_model_kernel(
+__global__ __launch_bounds__(kFwdBlock) void forward_kernel(
     const T *__restrict__ xr, const T *__restrict__ xc, T *__restrict__ y,
     const AngleParams *__restrict__ ang, int N, int S, int n_ang, int n_det, double ds,
     double s0, const DevState *st, int k, FwdShape sh)
@@ -144,10 +132,7 @@ __global__ __launch_bounds__(kFwdBlock) void forward_model_kernel(
     const int a = sh.wave_angle(wave);
     if (a >= n_ang) return;
     const int i = sh.lane_ray(wave);
-    if constexpr (MODEL == ABG_FP_STRIP)
-        forward_ray_strip(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
-    else
-        forward_ray_joseph(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
+    forward_ray<T, MODEL>(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
 }
 
 // 64 angles staged per round: the smaller LDS footprint lets more blocks share a CU
@@ -237,7 +222,7 @@ hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStr
     const double s0 = -0.5 * (g.n_det - 1) * g.ds;
     // timed at the kernel's own start and end when profiling is on
     ProfScope ps(kProfFwd, s, st ? k : 0, true);
-    if (g.model == ABG_FP_LINE && plan.nw > 0) {
+    if (g.model != ABG_FP_STRIP && plan.nw > 0) {
         FwdOrder ord{(g.n_det + 63) / 64, (g.n_ang + plan.nw - 1) / plan.nw, 0, 0};
         size_t blocks = (size_t)ord.ngx * ord.ngy;
         if (plan.tiled) {
@@ -245,7 +230,12 @@ hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStr
             ord.cols = ord.ngx + (6 - ord.ngx % 4) % 4;
             blocks = ((size_t)ord.cols * kFwdTileRows + 7) / 8 * 8 * ord.rows;
         }
-        auto fn = plan.nw == 8 ? forward_staged_kernel<T, 8> : forward_staged_kernel<T, 4>;
+        auto pick = [&](auto model) {
+            constexpr int M = decltype(model)::value;
+            return plan.nw == 8 ? forward_staged_kernel<T, 8, M> : forward_staged_kernel<T, 4, M>;
+        };
+        auto fn = g.model == ABG_FP_LINE ? pick(std::integral_constant<int, ABG_FP_LINE>{})
+                                         : pick(std::integral_constant<int, ABG_FP_JOSEPH>{});
         hipExtLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(64 * plan.nw), 0, s, ps.e0, ps.e1, 0,
                               (const T *)xr, (const T *)xc, static_cast<T *>(y),
                               (const AngleParams *)g.dev, N, S, g.n_ang, g.n_det, g.ds, s0, st, k,
@@ -255,9 +245,9 @@ hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStr
     const FwdShape sh{plan.lg};
     const int apb = 1 << sh.lg_apb, rays = kFwdBlock >> sh.lg_apb;
     dim3 grid((g.n_det + rays - 1) / rays, (g.n_ang + apb - 1) / apb);
-    auto fn = g.model == ABG_FP_STRIP    ? forward_model_kernel<T, ABG_FP_STRIP>
-              : g.model == ABG_FP_JOSEPH ? forward_model_kernel<T, ABG_FP_JOSEPH>
-                                         : forward_kernel<T>;
+    auto fn = g.model == ABG_FP_STRIP    ? forward_kernel<T, ABG_FP_STRIP>
+              : g.model == ABG_FP_JOSEPH ? forward_kernel<T, ABG_FP_JOSEPH>
+                                         : forward_kernel<T, ABG_FP_LINE>;
     hipExtLaunchKernelGGL(fn, grid, dim3(kFwdBlock), 0, s, ps.e0, ps.e1, 0,
                           (const T *)xr, (const T *)xc, static_cast<T *>(y),
                           (const AngleParams *)g.dev, N, S, g.n_ang, g.n_det, g.ds, s0, st,

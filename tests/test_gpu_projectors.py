@@ -135,7 +135,8 @@ STAGED_GEOMS = [
 
 @pytest.mark.parametrize("kw", STAGED_GEOMS, ids=_ids)
 @pytest.mark.parametrize("dt", ["f64", "f32"])
-def test_forward_staged_launches_bit_identical(gpu_lib, kw, dt):
+@pytest.mark.parametrize("model", ["line", "joseph"])
+def test_forward_staged_launches_bit_identical(gpu_lib, kw, dt, model):
     """The staged launches write every ray once and give the bits of the direct kernel
     (one angle per block), which the oracle tests pin."""
     import torch
@@ -143,7 +144,7 @@ def test_forward_staged_launches_bit_identical(gpu_lib, kw, dt):
     tdt = torch.float64 if dt == "f64" else torch.float32
     rng = np.random.default_rng(6)
     x = torch.tensor(rng.standard_normal(kw["N"] ** 2), dtype=tdt, device="cuda")
-    gg = abg.Geometry(**kw)
+    gg = abg.Geometry(**kw, model=model)
     y = torch.full((gg.m,), float("nan"), dtype=tdt, device="cuda")
     try:
         gg.fp(x, out=y)
