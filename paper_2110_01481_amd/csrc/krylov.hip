@@ -26,7 +26,7 @@ namespace abg {
 namespace {
 
 constexpr int kCombU = 4;
-constexpr int kCombJ = 4;   // basis columns per trip of the combination
+constexpr int kCombJ = 8;   // basis columns per trip of the combination
 
 // Ranks are handed out in the order blocks start, so the blocks holding ranks are
 // running; a group no larger than the blocks the device holds at once always completes
@@ -191,46 +191,24 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(const TB *__restrict__ 
     }
     for (int j = threadIdx.x; j < kk; j += kBlock) cf[j] = sgn * coef[j];
     __syncthreads();
-    // each thread combines kCombU elements per trip, all of a column's loads in flight
-    const long long T = (long long)gridDim.x * kBlock;
+    // a block takes kCombU * kBlock consecutive elements per trip, kCombU per thread
+    constexpr int kTrip = kCombU * kBlock;
     double ss = 0.0;
-    for (long long l0 = (long long)blockIdx.x * kBlock + threadIdx.x; l0 < L; l0 += kCombU * T) {
+    for (long long l0 = (long long)blockIdx.x * kTrip + threadIdx.x; l0 < L;
+         l0 += (long long)gridDim.x * kTrip) {
         double acc[kCombU];
         bool in[kCombU];
 #pragma unroll
         for (int u = 0; u < kCombU; ++u) {
-            const long long l = l0 + u * T;
+            const long long l = l0 + u * kBlock;
             in[u] = l < L;
             acc[u] = (in[u] && base) ? bcoef * to_f64(base[l]) : 0.0;
         }
-        // four columns' loads in flight at once; each element still sums over j in order
-        int j = 0;
-        for (; j + kCombJ <= kk; j += kCombJ) {
-            double x[kCombJ][kCombU];
-#pragma unroll
-            for (int jj = 0; jj < kCombJ; ++jj) {
-                const TV *v = V + (size_t)(j + jj) * ldv + l0;
-#pragma unroll
-                for (int u = 0; u < kCombU; ++u) x[jj][u] = in[u] ? to_f64(v[u * T]) : 0.0;
-            }
-#pragma unroll
-            for (int jj = 0; jj < kCombJ; ++jj) {
-#pragma unroll
-                for (int u = 0; u < kCombU; ++u) acc[u] = fma(cf[j + jj], x[jj][u], acc[u]);
-            }
-        }
-        for (; j < kk; ++j) {
-            const TV *v = V + (size_t)j * ldv + l0;
-            double x[kCombU];
-#pragma unroll
-            for (int u = 0; u < kCombU; ++u) x[u] = in[u] ? to_f64(v[u * T]) : 0.0;
-#pragma unroll
-            for (int u = 0; u < kCombU; ++u) acc[u] = fma(cf[j], x[u], acc[u]);
-        }
+        combine_columns<kCombJ>(V + l0, ldv, kBlock, kk, cf, in, acc);
 #pragma unroll
         for (int u = 0; u < kCombU; ++u) {
             if (in[u]) {
-                out[l0 + u * T] = (TO)acc[u];
+                out[l0 + u * kBlock] = (TO)acc[u];
                 ss = fma(acc[u], acc[u], ss);
             }
         }
@@ -240,13 +218,10 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(const TB *__restrict__ 
     ss = block_sum(ss, lds);
     if (threadIdx.x == 0) {
         agent_store(partials + blockIdx.x, ss);
-        const unsigned prev = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-        last = prev == gridDim.x - 1;
+        last = count_in(count, gridDim.x);
     }
     __syncthreads();
     if (!last) return;
-    last_block_fence();
     double t = 0.0;
     for (int j = threadIdx.x; j < (int)gridDim.x; j += kBlock) t += agent_load(partials + j);
     t = block_sum(t, lds);

@@ -409,3 +409,23 @@ def test_long_runs_past_the_one_wave_givens(gpu_lib):
         assert np.all(dev <= bound), (c.method, j + 1, dev[j], bound[j])
         assert np.all(np.diff(ls) <= 1e-12 * ls[:-1])
         assert abs(r.res_norm - ref.res_norms[-1]) <= bound[-1] * ref.res_norms[-1]
+
+
+@pytest.mark.parametrize("method", ["ab", "ba"])
+@pytest.mark.parametrize("N,n_ang,n_det", [(16, 20, 23), (16, 32, 32), (16, 41, 25), (64, 4100, 129)])
+def test_round_residual_norm_at_chunk_edges(gpu_lib, method, N, n_ang, n_det):
+    """The norm a round publishes (chunked combination of nine or ten columns) equals the
+    explicit ||b - A x_9|| of the same iterate: sinograms below one chunk, of exactly one
+    chunk, of one more element, and of more chunks than the smallest chunk size allows.
+    FP64; the two differ by the rounding of nine projections and their combination, below
+    1e-11 of ||b||."""
+    import torch
+    abg = gpu_lib
+    gg = abg.Geometry(N, n_ang, n_det)
+    b = torch.tensor(np.random.default_rng(11).uniform(size=n_ang * n_det), dtype=torch.float64, device="cuda")
+    nb = float(b.norm())
+    p = abg.Problem(g=gg, method=method, b=b, k_max=9, stop="dp", tau=1.0, noise_norm=1e-9 * nb)
+    r = abg.batch_solve([p], proj="f64", basis="f64")[0]
+    assert r.k_done == 9
+    assert abs(r.res_hist[8] - r.res_norm) <= 1e-11 * nb
+    gg.close()
