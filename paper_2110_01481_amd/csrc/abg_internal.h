@@ -279,7 +279,7 @@ int gmres_error_history(const Geometry &g, int method, int kind, int k_max, abg_
 // Buffers inside a solve's workspace (the same layout as a single solve).
 struct InstanceView {
     void *V, *Z, *cur, *q, *rb0, *tm, *tn, *fpws;
-    double *H, *R, *cs, *sn, *g, *Y, *rho, *part, *mgs_part, *q64;
+    double *H, *R, *cs, *sn, *g, *Y, *rho, *part, *mgs_part, *q64, *gram;
     unsigned *count;
     long long L, ldv, mp, np;
     int part_cap;                 // doubles in part

@@ -7,8 +7,8 @@
 //   pad       BA: w_k -> padded image copies       AB: t = B w_k -> padded copies
 //   forward   BA: z = A w_k                        AB: q = A t
 //   back      AB: t = B w_k                        BA: q = B z
-//   mgs       modified Gram-Schmidt, one block group per problem (group barriers)
-//   givens    FP64 Givens update and y_k, one block per problem
+//   mgs       modified Gram-Schmidt, one block group per problem (group barriers), then
+//             the FP64 Givens update and y_k in the group's first block
 //   residual  ||r_k|| (BA: (b - A x0) - Z y_k; AB: W_{k+1}(beta e_1 - H y)) and the DP
 //             candidate test
 //
@@ -27,6 +27,7 @@
 #include <cmath>
 #include <cstring>
 #include <deque>
+#include <type_traits>
 #include <vector>
 
 #include "krylov_body.h"
@@ -54,7 +55,6 @@ enum Tab {
     kTMgsH,        // MGS groups with the largest register tile (FP32/BF16 basis)
     kTMgsX,        // streaming MGS groups (vectors the register tiles cannot hold)
     kTRes,         // residual chunks
-    kTGiv,         // one Givens block per problem
     kNumTab
 };
 
@@ -75,7 +75,7 @@ struct BatchInst {
     int method, kind, k_max, ld;
     long long L, ldv, mp, n, m;
     void *V, *Z, *cur, *q, *rb0, *tm, *tn, *xr, *xc;
-    double *H, *R, *cs, *sn, *g, *Y, *rho, *part, *mgs_part, *q64;
+    double *H, *R, *cs, *sn, *g, *Y, *rho, *part, *mgs_part, *q64, *gram;
     unsigned *count;
     double bd_rel;
     int mgs_rows;
@@ -136,7 +136,6 @@ __device__ int items_of(int t, const BatchInst &d, const Tiles &tl)
     case kTMgsX: return d.mgs_class == 2 ? d.mgs_G : 0;
     case kTMgsH: return d.mgs_class == 3 ? d.mgs_G : 0;
     case kTRes: return d.need_res ? d.n_chunks : 0;
-    case kTGiv: return 1;
     }
     return 0;
 }
@@ -447,6 +446,7 @@ __global__ __launch_bounds__(kBlock) void bmgs_kernel(const BatchInst *__restric
                                                       TabView tv, int t)
 {
     __shared__ double lds[kWaves];
+    __shared__ std::conditional_t<E == 0, int, IcwyLds> il;
     // at most `total` blocks can hold a ticket: the others leave without touching the
     // counter (a large, mostly idle grid would otherwise queue on it)
     if ((int)blockIdx.x >= tv.total[t]) return;
@@ -473,30 +473,23 @@ __global__ __launch_bounds__(kBlock) void bmgs_kernel(const BatchInst *__restric
         a.ticket = nullptr;
         a.q64 = gfield<double>(d.q64);
         a.set_beta = 0;
-        a.giv = GivensDev{};
-        a.gram = nullptr;   // the engine runs the plain sweep
+        a.giv = GivensDev{gfield<double>(d.H),
+                          gfield<double>(d.R),
+                          gfield<double>(d.cs),
+                          gfield<double>(d.sn),
+                          gfield<double>(d.g),
+                          gfield<double>(d.Y) + (size_t)(k - 1) * d.k_max,
+                          (d.method == ABG_METHOD_AB && d.need_res) ? gfield<double>(d.rho) : nullptr,
+                          d.ld,
+                          nullptr};
+        a.gram = E == 0 ? nullptr : gfield<double>(d.gram);
         if constexpr (E == 0) mgs_stream_body<TX, TV>(a, rank, d.mgs_G, lds);
-        else mgs_body<TX, TV, E>(a, rank, d.mgs_G, lds);
+        else mgs_body<TX, TV, E>(a, rank, d.mgs_G, lds, &il);
+        // the Givens update by rank 0, unless this step raised an error
+        if (rank != 0) continue;
+        __syncthreads();
+        if (!halted(st, k)) mgs_tail(a, rank);
     }
-}
-
-__global__ __launch_bounds__(64) void bgivens_kernel(const BatchInst *__restrict__ D, DevState *S, TabView tv)
-{
-    if ((int)blockIdx.x >= tv.nseg[kTGiv]) return;
-    const int slot = tv.seg_slot(kTGiv, blockIdx.x);
-    const BatchInst &d = D[slot];
-    DevState *st = S + slot;
-    const int k = st->kcur;
-    if (halted(st, k)) return;
-    double *rho = (d.method == ABG_METHOD_AB && d.need_res) ? gfield<double>(d.rho) : nullptr;
-    if (k <= kWaveGivensMax)
-        givens_wave(gfield<double>(d.H), d.ld, gfield<double>(d.R), gfield<double>(d.cs),
-                    gfield<double>(d.sn), gfield<double>(d.g),
-                    gfield<double>(d.Y) + (size_t)(k - 1) * d.k_max, rho, st->beta, k, st);
-    else
-        givens_step(gfield<double>(d.H), d.ld, gfield<double>(d.R), gfield<double>(d.cs),
-                    gfield<double>(d.sn), gfield<double>(d.g),
-                    gfield<double>(d.Y) + (size_t)(k - 1) * d.k_max, rho, st->beta, k, st);
 }
 
 // ||r_k|| by chunks: BA r = (b - A x0) - Z y_k, AB r = W_{k+1} rho. Each chunk's sum of
@@ -810,7 +803,6 @@ struct Engine {
         if constexpr (sizeof(TV) < 8)
             bmgs_kernel<TX, TV, kMgsHugeE><<<grid_mgs_h, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsH);
         bmgs_kernel<TX, TV, 0><<<grid_mgs_x, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsX);
-        bgivens_kernel<<<max_slots, 64, 0, q>>>(d_desc, d_st, tv);
         bres_kernel<TX, TV><<<grid_res, kBlock, 0, q>>>(d_desc, d_st, tv, tiles);
     }
 
@@ -921,6 +913,7 @@ struct Engine {
         d.part = v.part;
         d.mgs_part = v.mgs_part;
         d.q64 = v.q64;
+        d.gram = v.gram;
         d.mgs_rows = v.mgs_rows;
         d.count = v.count;
         d.bd_rel = (p.basis == ABG_F64 && p.proj == ABG_F64) ? 1e-14 : 1e-6;

@@ -477,6 +477,7 @@ InstanceView instance_view(const Geometry &g, int method, int k_max, abg_precisi
     v.part = reinterpret_cast<double *>(W + ly.part);
     v.mgs_part = reinterpret_cast<double *>(W + ly.mgs_part);
     v.q64 = ly.q64 ? reinterpret_cast<double *>(W + ly.q64) : nullptr;
+    v.gram = reinterpret_cast<double *>(W + ly.gram);
     v.count = reinterpret_cast<unsigned *>(W + ly.count);
     v.L = ly.L;
     v.ldv = ly.ldv;

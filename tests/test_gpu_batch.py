@@ -429,3 +429,24 @@ def test_round_residual_norm_at_chunk_edges(gpu_lib, method, N, n_ang, n_det):
     assert r.k_done == 9
     assert abs(r.res_hist[8] - r.res_norm) <= 1e-11 * nb
     gg.close()
+
+
+@pytest.mark.parametrize("N,n_ang,n_det", [(45, 32, 64), (46, 33, 63), (512, 8, 725), (513, 8, 727)])
+@pytest.mark.parametrize("method", ["ab", "ba"])
+def test_orthogonalisation_at_group_edges(gpu_lib, method, N, n_ang, n_det):
+    """Engine against single solve, FP64, six steps without a stopping rule, at vector
+    lengths on both sides of a group of one block (2048 elements) and of the largest group
+    of the small register tile (262144): the residual histories of the projected problem
+    agree within 1e-9 (both run the same recurrence, with sums in a different order)."""
+    import torch
+    abg = gpu_lib
+    gg = abg.Geometry(N, n_ang, n_det)
+    b = torch.tensor(np.random.default_rng(12).uniform(size=n_ang * n_det), dtype=torch.float64, device="cuda")
+    kw = dict(stop="none")
+    f = abg.ab_gmres if method == "ab" else abg.ba_gmres
+    s = f(gg, b, 6, **kw)
+    p = abg.Problem(g=gg, method=method, b=b, k_max=6, **kw)
+    r = abg.batch_solve([p], proj="f64", basis="f64")[0]
+    assert r.k_done == s.k_done == 6
+    assert np.allclose(r.ls_hist, s.ls_hist, rtol=1e-9, atol=0.0)
+    gg.close()
