@@ -174,7 +174,6 @@ hipError_t launch_givens(double *H, int ld, double *R, double *cs, double *sn, d
                          double *y, double *rho, const double *beta, int k, DevState *st,
                          hipStream_t s, DevState *snap = nullptr);
 // st->beta = st->hnext after the initial normalisation, or the zero-right-hand-side stop.
-hipError_t launch_set_beta(DevState *st, hipStream_t s);
 // Clears the stop flag (after a DP candidate that the explicit residual rejected).
 hipError_t launch_clear_stop(DevState *st, hipStream_t s);
 void set_mgs_target_blocks(int blocks);
@@ -288,10 +287,10 @@ struct InstanceView {
 };
 InstanceView instance_view(const Geometry &g, int method, int k_max, abg_precision p,
                            abg_stop st, void *ws);
-// Enqueues the initialisation (clears, r0, MGS step 0 into *dst); no host wait.
+// Enqueues the initialisation (*dst = init, clears, r0, MGS step 0, beta); no host wait.
 int instance_init(const Geometry &g, int method, int kind, int k_max, abg_stop st,
-                  abg_precision p, void *ws, const void *b, const void *x0, DevState *dst,
-                  hipStream_t s);
+                  abg_precision p, void *ws, const void *b, const void *x0, const DevState &init,
+                  DevState *dst, hipStream_t s);
 // Enqueues x = x_k (k = 0: x0 or zero) and ||b - A x|| into *lit; no host wait.
 int instance_form_x(const Geometry &g, int method, int kind, int k_max, abg_stop st,
                     abg_precision p, void *ws, int k, const void *b, const void *x0, void *x,

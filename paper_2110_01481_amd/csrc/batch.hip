@@ -13,8 +13,10 @@
 //             candidate test
 //
 // The work lists live in device memory and are rebuilt by `begin` every round, so the
-// graph never changes while problems join and leave (two variants are kept: the AB and
-// BA projector chains in sequence, or as two branches while the problems are small). Blocks take work items from a
+// graph does not change while problems join and leave (two variants are kept: the AB and
+// BA projector chains in sequence, or as two branches while the problems are small); it is
+// captured again when a problem first needs a list that no earlier one did. Rounds queue
+// behind one another without a host wait between them. Blocks take work items from a
 // per-list ticket counter; an item's arithmetic depends only on its own problem, so a
 // problem's results are the same alone and in any mix.
 //
@@ -563,17 +565,17 @@ __global__ __launch_bounds__(kBlock) void bres_kernel(const BatchInst *__restric
 }
 
 // ---- per-problem control kernels (launched by the host between rounds) ------------------
-__global__ void activate_kernel(DevState *st)
+// The descriptor of an admitted problem (a launch argument: no copy from host memory).
+__global__ void admit_kernel(const BatchInst d, BatchInst *slot)
 {
-    if (threadIdx.x != 0 || st->error) return;
-    if (st->hnext == 0.0) {
-        st->stop = 1;
-        st->stop_k = 0;
-        st->stop_reason = kStopZero;
-        return;
-    }
-    st->beta = st->hnext;
-    st->active = 1;
+    if (threadIdx.x == 0) *slot = d;
+}
+
+// Copy of every slot's scalars in the host's snapshot ring.
+__global__ void snap_kernel(const unsigned long long *src, unsigned long long *dst, int n)
+{
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < n) dst[i] = src[i];
 }
 
 // After x_{stop_k} and lit = ||b - A x|| were formed for a DP candidate: accept, finish
@@ -629,9 +631,8 @@ constexpr int kSnapRing = 4;
         if (e_ != hipSuccess) return fail(ABG_EHIP); \
     } while (0)
 
-// Stream callback after an engine round: returns the round's share of the Gram-Schmidt
-// budget (touches only the budget object, no HIP call).
-void release_round(void *budget) { static_cast<GroupBudget *>(budget)->release(GroupBudget::kUnits); }
+// Stream callback after an engine round (makes no HIP call).
+void release_round(void *hold) { static_cast<RoundHold *>(hold)->give(); }
 
 }  // namespace
 
@@ -652,6 +653,8 @@ struct Engine {
     abg_precision p{};
     int max_slots = 0, device = 0;
     hipStream_t s = nullptr, cap_stream = nullptr;
+    hipStream_t cb_stream = nullptr;   // the callbacks that return a round's hold
+    RoundHold hold;
     // second captured stream and the events that fork the AB chain onto it and join it
     hipStream_t cap_stream2 = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
@@ -659,8 +662,6 @@ struct Engine {
     DevState *d_st = nullptr;
     int *d_tab = nullptr;
     TabView tv{};
-    BatchInst *h_desc = nullptr;     // pinned staging, one per slot
-    DevState *h_init = nullptr;      // pinned staging, one per slot
     DevState *h_snap = nullptr;      // pinned ring of snapshots
     hipEvent_t ev[kSnapRing] = {};
     std::deque<int> inflight;
@@ -669,6 +670,7 @@ struct Engine {
     hipGraph_t graph[2] = {};
     hipGraphExec_t exec[2] = {};
     bool dirty = true;
+    unsigned need = 0;   // lists (bit t: list t) that a submitted problem has needed
     Tiles tiles{0, 64, 2};
     int grid_proj = 0, grid_back = 0, grid_back64 = 0, grid_back_adj = 0, grid_back64_adj = 0;
     int grid_mgs_s = 0, grid_mgs_l = 0, grid_res = 0;
@@ -689,6 +691,10 @@ struct Engine {
     ~Engine()
     {
         if (s) (void)hipStreamSynchronize(s);
+        if (cb_stream) {
+            (void)hipStreamSynchronize(cb_stream);
+            (void)hipStreamDestroy(cb_stream);
+        }
         for (int v = 0; v < 2; ++v) {
             if (exec[v]) (void)hipGraphExecDestroy(exec[v]);
             if (graph[v]) (void)hipGraphDestroy(graph[v]);
@@ -704,8 +710,6 @@ struct Engine {
         if (d_desc) (void)hipFree(d_desc);
         if (d_st) (void)hipFree(d_st);
         if (d_tab) (void)hipFree(d_tab);
-        if (h_desc) (void)hipHostFree(h_desc);
-        if (h_init) (void)hipHostFree(h_init);
         if (h_snap) (void)hipHostFree(h_snap);
     }
 
@@ -746,17 +750,23 @@ struct Engine {
         return capacities<float, bf16>();
     }
 
+    bool needs(int t) const { return need >> t & 1u; }
+
     // list t (interpolating back projector) and list t + 1 (its matched-pair twin)
     template <typename TX> void enqueue_back(hipStream_t q, const Tiles &tl, int t, int mode)
     {
         if (tl.ang_block == 64) {
-            bback_kernel<TX, 64, false><<<grid_back64, kBackThreads, 0, q>>>(d_desc, d_st, tv, t, mode, tl);
-            bback_kernel<TX, 64, true><<<grid_back64_adj, kBackThreads, 0, q>>>(d_desc, d_st, tv, t + 1,
-                                                                                mode, tl);
+            if (needs(t))
+                bback_kernel<TX, 64, false><<<grid_back64, kBackThreads, 0, q>>>(d_desc, d_st, tv, t, mode, tl);
+            if (needs(t + 1))
+                bback_kernel<TX, 64, true><<<grid_back64_adj, kBackThreads, 0, q>>>(d_desc, d_st, tv, t + 1,
+                                                                                    mode, tl);
         } else {
-            bback_kernel<TX, 128, false><<<grid_back, kBackThreads, 0, q>>>(d_desc, d_st, tv, t, mode, tl);
-            bback_kernel<TX, 128, true><<<grid_back_adj, kBackThreads, 0, q>>>(d_desc, d_st, tv, t + 1,
-                                                                               mode, tl);
+            if (needs(t))
+                bback_kernel<TX, 128, false><<<grid_back, kBackThreads, 0, q>>>(d_desc, d_st, tv, t, mode, tl);
+            if (needs(t + 1))
+                bback_kernel<TX, 128, true><<<grid_back_adj, kBackThreads, 0, q>>>(d_desc, d_st, tv, t + 1,
+                                                                                   mode, tl);
         }
     }
 
@@ -764,26 +774,29 @@ struct Engine {
     // round's z, t and q from w_k without advancing any problem). The BA chain (pad,
     // forward, back) and the AB chain (back, pad, forward) touch disjoint problems and
     // lists; with q2 the AB chain forks onto q2 and joins q after its last phase, so that
-    // in a captured round the two chains are independent branches of the graph.
+    // in a captured round the two chains are independent branches of the graph. A list that
+    // no problem has needed so far is not launched at all (an empty launch costs 2-5 us of
+    // a round).
     template <typename TX> void enqueue_projectors_t(hipStream_t q, const Tiles &tl,
                                                      hipStream_t q2 = nullptr)
     {
         begin_kernel<<<kNumTab, 256, 0, q>>>(d_desc, d_st, tv, max_slots, tl);
         Tiles tf = tl;
         tf.stage = fwd_stage_share();
-        hipStream_t qa = q;
-        if (q2) {
+        const bool ba = needs(kTFwdBA), ab = needs(kTFwdAB);
+        const bool fork = q2 && ba && ab;
+        const hipStream_t qa = fork ? q2 : q;
+        if (fork) {
             (void)hipEventRecord(fork_ev, q);
             (void)hipStreamWaitEvent(q2, fork_ev, 0);
-            qa = q2;
         }
-        bpad_kernel<TX><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, kTPadBA, 0, tl);
-        enqueue_back<TX>(qa, tl, kTBackAB, 0);
-        bfwd_kernel<TX><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, kTFwdBA, 0, tf);
-        bpad_kernel<TX><<<grid_proj, 256, 0, qa>>>(d_desc, d_st, tv, kTPadAB, 1, tl);
-        enqueue_back<TX>(q, tl, kTBackBA, 1);
-        bfwd_kernel<TX><<<grid_proj, 256, 0, qa>>>(d_desc, d_st, tv, kTFwdAB, 1, tf);
-        if (q2) {
+        if (ba) bpad_kernel<TX><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, kTPadBA, 0, tl);
+        if (ab) enqueue_back<TX>(qa, tl, kTBackAB, 0);
+        if (ba) bfwd_kernel<TX><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, kTFwdBA, 0, tf);
+        if (ab) bpad_kernel<TX><<<grid_proj, 256, 0, qa>>>(d_desc, d_st, tv, kTPadAB, 1, tl);
+        if (ba) enqueue_back<TX>(q, tl, kTBackBA, 1);
+        if (ab) bfwd_kernel<TX><<<grid_proj, 256, 0, qa>>>(d_desc, d_st, tv, kTFwdAB, 1, tf);
+        if (fork) {
             (void)hipEventRecord(join_ev, q2);
             (void)hipStreamWaitEvent(q, join_ev, 0);
         }
@@ -798,12 +811,16 @@ struct Engine {
     template <typename TX, typename TV> void enqueue_round_t(hipStream_t q, hipStream_t q2)
     {
         enqueue_projectors_t<TX>(q, tiles, q2);
-        bmgs_kernel<TX, TV, kMgsSmallE><<<grid_mgs_s, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsS);
-        bmgs_kernel<TX, TV, kMgsLargeE><<<grid_mgs_l, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsL);
-        if constexpr (sizeof(TV) < 8)
-            bmgs_kernel<TX, TV, kMgsHugeE><<<grid_mgs_h, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsH);
-        bmgs_kernel<TX, TV, 0><<<grid_mgs_x, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsX);
-        bres_kernel<TX, TV><<<grid_res, kBlock, 0, q>>>(d_desc, d_st, tv, tiles);
+        if (needs(kTMgsS))
+            bmgs_kernel<TX, TV, kMgsSmallE><<<grid_mgs_s, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsS);
+        if (needs(kTMgsL))
+            bmgs_kernel<TX, TV, kMgsLargeE><<<grid_mgs_l, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsL);
+        if constexpr (sizeof(TV) < 8) {
+            if (needs(kTMgsH))
+                bmgs_kernel<TX, TV, kMgsHugeE><<<grid_mgs_h, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsH);
+        }
+        if (needs(kTMgsX)) bmgs_kernel<TX, TV, 0><<<grid_mgs_x, kBlock, 0, q>>>(d_desc, d_st, tv, kTMgsX);
+        if (needs(kTRes)) bres_kernel<TX, TV><<<grid_res, kBlock, 0, q>>>(d_desc, d_st, tv, tiles);
     }
 
     void enqueue_round(hipStream_t q, hipStream_t q2)
@@ -833,6 +850,8 @@ struct Engine {
     int capture(int v)
     {
         if (dirty) {
+            // a round of the old graph may still be running
+            if (exec[0] || exec[1]) BCK(hipStreamSynchronize(s));
             for (int u = 0; u < 2; ++u) {
                 if (exec[u]) BCK(hipGraphExecDestroy(exec[u]));
                 if (graph[u]) BCK(hipGraphDestroy(graph[u]));
@@ -965,15 +984,22 @@ struct Engine {
         DevState init{};
         init.gen = sl.gen;
         init.dp_thr = r.stop.kind == ABG_STOP_DP ? sl.thr * (1.0 + slack) : 0.0;
-        h_desc[sidx] = d;
-        h_init[sidx] = init;
-        BCK(hipMemcpyAsync(d_desc + sidx, h_desc + sidx, sizeof(BatchInst), hipMemcpyHostToDevice, s));
-        BCK(hipMemcpyAsync(d_st + sidx, h_init + sidx, sizeof(DevState), hipMemcpyHostToDevice, s));
-        int rc = instance_init(g, r.method, r.bp_kind, r.k_max, r.stop, p, r.ws, r.b, r.x0,
-                               d_st + sidx, s);
-        if (rc != ABG_OK) return fail(rc);
-        activate_kernel<<<1, 64, 0, s>>>(d_st + sidx);
+        admit_kernel<<<1, 64, 0, s>>>(d, d_desc + sidx);
         BCK(hipGetLastError());
+        const int rc = instance_init(g, r.method, r.bp_kind, r.k_max, r.stop, p, r.ws, r.b, r.x0, init,
+                                     d_st + sidx, s);
+        if (rc != ABG_OK) return fail(rc);
+        // the captured rounds hold the launches of the lists that some problem has needed
+        unsigned lists = need | 1u << (d.mgs_class == 0 ? kTMgsS : d.mgs_class == 1 ? kTMgsL
+                                                               : d.mgs_class == 3 ? kTMgsH : kTMgsX);
+        const bool ba = r.method == ABG_METHOD_BA, adj = r.bp_kind == ABG_BP_ADJ;
+        lists |= ba ? 1u << kTPadBA | 1u << kTFwdBA | 1u << (adj ? kTBackBAAdj : kTBackBA)
+                    : 1u << kTPadAB | 1u << kTFwdAB | 1u << (adj ? kTBackABAdj : kTBackAB);
+        if (d.need_res) lists |= 1u << kTRes;
+        if (lists != need) {
+            need = lists;
+            dirty = true;
+        }
         sl.phase = kRunning;
         if (r.info) {
             r.info->k_stop = r.info->k_done = r.info->n_literal = 0;
@@ -1157,30 +1183,44 @@ struct Engine {
             int rc = wait_oldest();
             if (rc) return rc;
         }
+        bool held = false;
         if (n_in(kRunning) > 0) {
             const int v = fork_chains() ? 1 : 0;
             if (dirty || !exec[v]) {
                 int rc = capture(v);
                 if (rc) return rc;
             }
-            // the round's Gram-Schmidt grids take what the device holds: the whole
-            // budget, returned by a stream callback once the round has run
-            GroupBudget &budget = device_group_budget();
-            budget.acquire(GroupBudget::kUnits);
-            hipError_t e = hipGraphLaunch(exec[v], s);
-            if (e == hipSuccess) e = hipLaunchHostFunc(s, release_round, &budget);
+            // the round's Gram-Schmidt grids take what the device holds
+            hold.take(device_group_budget());
+            const hipError_t e = hipGraphLaunch(exec[v], s);
             if (e != hipSuccess) {
                 (void)hipStreamSynchronize(s);
-                budget.release(GroupBudget::kUnits);
+                hold.give();
                 return fail(ABG_EHIP);
             }
             ++rounds;
+            held = true;
         }
         const int r = ring_next;
         ring_next = (ring_next + 1) % kSnapRing;
-        BCK(hipMemcpyAsync(h_snap + (size_t)r * max_slots, d_st, sizeof(DevState) * max_slots,
-                           hipMemcpyDeviceToHost, s));
-        BCK(hipEventRecord(ev[r], s));
+        static_assert(sizeof(DevState) % 8 == 0, "copied in words of eight bytes");
+        const int words = (int)(sizeof(DevState) / 8) * max_slots;
+        snap_kernel<<<(words + 255) / 256, 256, 0, s>>>(
+            reinterpret_cast<const unsigned long long *>(d_st),
+            reinterpret_cast<unsigned long long *>(h_snap + (size_t)r * max_slots), words);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipEventRecord(ev[r], s);
+        // the hold is returned from a stream of its own, so that the next round's launches
+        // do not wait for the callback
+        if (held) {
+            if (e == hipSuccess) e = hipStreamWaitEvent(cb_stream, ev[r], 0);
+            if (e == hipSuccess) e = hipLaunchHostFunc(cb_stream, release_round, &hold);
+            if (e != hipSuccess) {
+                (void)hipStreamSynchronize(s);
+                hold.give();
+            }
+        }
+        if (e != hipSuccess) return fail(ABG_EHIP);
         inflight.push_back(r);
         return ABG_OK;
     }
@@ -1212,6 +1252,7 @@ int engine_create(abg_precision p, int max_slots, hipStream_t s, Engine **out)
     };
     if (hipGetDevice(&e->device) != hipSuccess) return bad();
     if (hipStreamCreateWithFlags(&e->cap_stream, hipStreamNonBlocking) != hipSuccess) return bad();
+    if (hipStreamCreateWithFlags(&e->cb_stream, hipStreamNonBlocking) != hipSuccess) return bad();
     if (hipStreamCreateWithFlags(&e->cap_stream2, hipStreamNonBlocking) != hipSuccess) return bad();
     if (hipEventCreateWithFlags(&e->fork_ev, hipEventDisableTiming) != hipSuccess) return bad();
     if (hipEventCreateWithFlags(&e->join_ev, hipEventDisableTiming) != hipSuccess) return bad();
@@ -1219,8 +1260,6 @@ int engine_create(abg_precision p, int max_slots, hipStream_t s, Engine **out)
     if (hipMalloc(&e->d_desc, sizeof(BatchInst) * max_slots) != hipSuccess) return bad();
     if (hipMalloc(&e->d_st, sizeof(DevState) * max_slots) != hipSuccess) return bad();
     if (hipMalloc(&e->d_tab, sizeof(int) * tab_ints) != hipSuccess) return bad();
-    if (hipHostMalloc((void **)&e->h_desc, sizeof(BatchInst) * max_slots, hipHostMallocDefault) != hipSuccess) return bad();
-    if (hipHostMalloc((void **)&e->h_init, sizeof(DevState) * max_slots, hipHostMallocDefault) != hipSuccess) return bad();
     if (hipHostMalloc((void **)&e->h_snap, sizeof(DevState) * max_slots * kSnapRing, hipHostMallocDefault) != hipSuccess) return bad();
     for (auto &ev : e->ev)
         if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return bad();

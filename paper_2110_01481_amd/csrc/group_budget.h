@@ -55,6 +55,14 @@ public:
         cv_.notify_all();
     }
 
+    // Whether a request is waiting (its holder-to-be is then served before any extension
+    // of a share that is held).
+    bool contended() const
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        return next_ != serving_;
+    }
+
     long long in_use() const
     {
         std::lock_guard<std::mutex> lk(mu_);
@@ -66,6 +74,40 @@ private:
     std::condition_variable cv_;
     long long used_ = 0;
     unsigned long long next_ = 0, serving_ = 0;
+};
+
+// The whole budget held over a sequence of rounds that follow one another on one stream,
+// each given back by a callback once it has run. A round enqueued while an earlier one is
+// still held extends that hold instead of waiting for its callback (that wait left the
+// device idle for 70-100 us per round of an engine); if anyone else waits for the budget,
+// the round queues behind them. take() is called by one thread at a time, give() by any.
+class RoundHold {
+public:
+    void take(GroupBudget &b)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (rounds_ > 0 && !b.contended()) {
+                ++rounds_;
+                return;
+            }
+        }
+        b.acquire(GroupBudget::kUnits);   // returns once the earlier rounds are given back
+        std::lock_guard<std::mutex> lk(mu_);
+        budget_ = &b;
+        ++rounds_;
+    }
+
+    void give()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (--rounds_ == 0) budget_->release(GroupBudget::kUnits);
+    }
+
+private:
+    std::mutex mu_;
+    GroupBudget *budget_ = nullptr;
+    int rounds_ = 0;
 };
 
 }  // namespace abg

@@ -327,20 +327,6 @@ __global__ __launch_bounds__(64) void givens_kernel(double *H, int ld, double *R
     if (snap && threadIdx.x == 0) *snap = *st;
 }
 
-// After the initial normalisation: beta = ||r_0|| for the later steps, or (r_0 = 0) the
-// zero-right-hand-side stop before step 1.
-__global__ void set_beta_kernel(DevState *st)
-{
-    if (threadIdx.x != 0 || st->error) return;
-    if (st->hnext == 0.0) {
-        st->stop = 1;
-        st->stop_k = 0;
-        st->stop_reason = kStopZero;
-    } else {
-        st->beta = st->hnext;
-    }
-}
-
 __global__ void clear_stop_kernel(DevState *st)
 {
     if (threadIdx.x == 0) {
@@ -530,12 +516,6 @@ hipError_t launch_sub_norm(int t, const void *a, const void *b, void *out, long 
 hipError_t launch_reduce_sqrt(const double *partials, int nb, double *dst, hipStream_t s)
 {
     reduce_sqrt_kernel<<<1, kBlock, 0, s>>>(partials, nb, dst);
-    return hipGetLastError();
-}
-
-hipError_t launch_set_beta(DevState *st, hipStream_t s)
-{
-    set_beta_kernel<<<1, 64, 0, s>>>(st);
     return hipGetLastError();
 }
 

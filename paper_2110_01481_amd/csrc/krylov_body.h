@@ -304,7 +304,7 @@ struct MgsDev {
     double bd_rel;
     int step;
     double *q64;       // FP64 scratch of the streaming variant (vectors longer than kRegMaxL)
-    int set_beta;      // step 0 of a single solve: beta = ||r_0||, or the zero-rhs stop
+    int set_beta;      // step 0: beta = ||r_0||, or the zero-rhs stop
     GivensDev giv;
     // strictly lower triangle of the basis Gram matrix, row i (<w_i, w_j>, j < i) packed
     // from i(i-1)/2; null: every step runs the plain sweep
@@ -605,8 +605,8 @@ __device__ inline void givens_wave_n(double *H, int ld, double *R, double *cs, d
     }
 }
 
-// After the normalisation, by the block of rank 0 of a single solve's launch: step 0
-// sets beta = ||r_0|| (or raises the zero-right-hand-side stop), step k >= 1 runs the
+// After the normalisation, by the block of rank 0: step 0 sets beta = ||r_0|| and
+// activates the solve (or raises the zero-right-hand-side stop), step k >= 1 runs the
 // Givens update of column k, then copies the scalars to the host slot.
 __device__ inline void mgs_tail(const MgsDev &a, int rank)
 {
@@ -619,6 +619,7 @@ __device__ inline void mgs_tail(const MgsDev &a, int rank)
             st->stop_reason = kStopZero;
         } else {
             st->beta = st->hnext;
+            st->active = 1;
         }
     }
     if (a.giv.H) {

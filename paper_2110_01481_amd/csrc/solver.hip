@@ -402,7 +402,7 @@ struct Solve {
     // Initialisation without a host synchronisation: scratch cleared, b - A x0,
     // r0 = (B)(b - A x0), and MGS step 0 (beta = ||r0|| into dst->hnext and g[0], w_1).
     // init: the solve's initial scalars (null: the caller owns *dst)
-    int init_async(const void *b, const void *x0, const DevState *init)
+    int init_async(const void *b, const void *x0, const DevState &init)
     {
         const long long m = g.m();
         // one launch: the scalars, empty reduction slots, zeroed counters, H and g, the
@@ -422,7 +422,7 @@ struct Solve {
             {rb0, x0 ? nullptr : b, words(ly.mp * sX), x0 ? 0ull : words(m * sX), 0u, 0u},
             {V, nullptr, words(ly.ldv * dtype_size(p.basis)), 0, 0u, 0u},
         };
-        CK(launch_init_fill(fr, (int)(sizeof fr / sizeof fr[0]), init, dst, s));
+        CK(launch_init_fill(fr, (int)(sizeof fr / sizeof fr[0]), &init, dst, s));
         if (x0) {
             RC(fwd(x0, tm));
             int nb = 0;
@@ -434,7 +434,7 @@ struct Solve {
             r0 = q;
         }
         MgsLaunch M0 = mgs_args(r0, 0);
-        M0.set_beta = init != nullptr;
+        M0.set_beta = 1;
         CK(launch_mgs(M0, s));
         return ABG_OK;
     }
@@ -490,12 +490,12 @@ InstanceView instance_view(const Geometry &g, int method, int k_max, abg_precisi
 }
 
 int instance_init(const Geometry &g, int method, int kind, int k_max, abg_stop st,
-                  abg_precision p, void *ws, const void *b, const void *x0, DevState *dst,
-                  hipStream_t s)
+                  abg_precision p, void *ws, const void *b, const void *x0, const DevState &init,
+                  DevState *dst, hipStream_t s)
 {
     Solve S(g, method, kind, k_max, st, p, s, ws);
     S.dst = dst;
-    return S.init_async(b, x0, nullptr);
+    return S.init_async(b, x0, init);
 }
 
 int instance_form_x(const Geometry &g, int method, int kind, int k_max, abg_stop st,
@@ -555,7 +555,7 @@ int run_solver(const Geometry &g, int method, int kind, const void *b, const voi
 
     // b - A x0, r0 = (B)(b - A x0), beta = ||r0|| into g[0], w_1; the host learns beta
     // (and a zero right-hand side or a NaN) from the scalars of step 1
-    RC(S.init_async(b, x0, &init));
+    RC(S.init_async(b, x0, init));
     DevState hs;
     bool zero_rhs = false;
     {

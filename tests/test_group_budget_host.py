@@ -16,3 +16,14 @@ def test_group_budget_checks(tmp_path):
                     "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
+
+
+def test_round_hold_checks(tmp_path):
+    """RoundHold: extension while nobody waits, a waiter served first, nothing lost."""
+    exe = tmp_path / "round_hold_check"
+    src = os.path.join(ROOT, "tests", "native", "round_hold_check.cpp")
+    inc = os.path.join(ROOT, "paper_2110_01481_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-Wall", "-Werror", "-I", inc, src,
+                    "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
