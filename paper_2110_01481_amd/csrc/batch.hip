@@ -41,6 +41,8 @@ namespace abg {
 // Work lists are split into kRanges contiguous ranges with a counter each (see
 // for_each_item); the list-order schedule claims at most kMaxListChunk items at a time.
 constexpr int kRanges = 8;
+constexpr int kClaims = 32;        // claim counters of a list
+constexpr int kClaimStride = 32;   // their distance in words: one cache line
 constexpr int kMaxListChunk = 8;
 
 enum Tab {
@@ -91,7 +93,7 @@ struct BatchInst {
 // consecutive tickets.
 struct TabView {
     int *nseg, *total;
-    unsigned *ticket;    // [kNumTab][kRanges]
+    unsigned *ticket;    // [kNumTab][kClaims], kClaimStride apart
     int *slot, *first;   // [kNumTab][max_slots]
     int max_slots;
     __device__ int seg_slot(int t, int i) const { return slot[t * max_slots + i]; }
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(256) void begin_kernel(const BatchInst *__restrict_
         tv.nseg[t] = tot_n;
         tv.total[t] = tot_c;
     }
-    if (tid < kRanges) tv.ticket[t * kRanges + tid] = 0u;
+    if (tid < kClaims) tv.ticket[(t * kClaims + tid) * kClaimStride] = 0u;
 }
 
 // Problem and item of ticket `it` of list t (binary search over the segments). Every
@@ -233,14 +235,19 @@ __device__ inline void locate(const TabView &tv, int t, int it, int *slot, int *
 //           guided: a claim takes half of what is left of the range divided by the blocks
 //           that start on it, so the last items go one at a time and a phase does not
 //           wait on one block's large final chunk (an item of a 2048^2 problem is ~0.1 ms).
-//  sched 2  list order: block b takes item b, then the blocks claim the items after the
-//           first `grid` through one counter in guided chunks (what is left over twice
-//           the grid, between 1 and kMaxListChunk items). The running blocks all work on
-//           the same one or two problems, as the blocks of a single solve's launch do, so
-//           only those problems' images and sinograms compete for the caches (with one
-//           range per XCD, or with chunks of ~100 items, eight or more large problems are
-//           in flight at once, more than the Infinity Cache holds, and a served batch ran
-//           15% slower); a list no longer than the grid takes no claim at all.
+//  sched 2  list order: block b takes item b, then claims of the items after the first
+//           `grid`: those at distance g, g + kClaims, ... belong to the blocks b with
+//           b % kClaims = g, which share a counter (of its own cache line) and take them in
+//           guided chunks (what is left over twice the blocks, between 1 and kMaxListChunk).
+//           A block claims its next chunk before it works on the present one. (Claims take
+//           about 56 ns each on one counter of the whole list: with that, twelve problems
+//           of 256^2 x 360, FP32, took 370 us in the forward phase, 130 now, and 174 in the back
+//           projection, 76 now.) The running blocks all work on the same one or two
+//           problems, as the blocks of a single solve's launch do, so only those problems'
+//           images and sinograms compete for the caches (with one range per XCD, or with
+//           chunks of ~100 items, eight or more large problems are in flight at once, more
+//           than the Infinity Cache holds, and a served batch ran 15% slower); a list no
+//           longer than the grid takes no claim at all.
 // The pad and residual lists (uniform, cheap items) always run sched 0.
 // A block's items come in increasing order, so the segment (problem) of an item is found
 // by moving a cursor forward. body must be called by the whole block (it may
@@ -264,36 +271,43 @@ __device__ inline void for_each_item(const TabView &tv, int t, int sched, F &&bo
     }
     const int G = min((int)gridDim.x, total);
     if (sched == 2) {
-        visit(blockIdx.x);
         const int rest = total - G;
-        if (rest <= 0) return;
-        unsigned *tk = tv.ticket + t * kRanges;
+        if (rest <= 0) {
+            visit(blockIdx.x);
+            return;
+        }
+        const int P = min(kClaims, G), g = (int)blockIdx.x % P;
+        const int n = (rest - g + P - 1) / P;         // this counter's items: G + g + P c, c < n
+        const int blocks = (G - g + P - 1) / P;       // that share it
+        unsigned *tk = tv.ticket + (t * kClaims + g) * kClaimStride;
+        auto chunk = [&](int done) { return min(kMaxListChunk, max(1, (n - done) / (2 * blocks))); };
+        unsigned claimed = 0;                         // thread 0: the next chunk's first c
+        auto claim = [&](int len) {
+            if (threadIdx.x == 0)
+                claimed = __hip_atomic_fetch_add(tk, (unsigned)len, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        };
+        int len = chunk(0);
+        claim(len);
+        visit(blockIdx.x);
         for (;;) {
             __syncthreads();
-            if (threadIdx.x == 0) {
-                int c = rest, len = 0;
-                const int seen =
-                    (int)__hip_atomic_load(tk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (seen < rest) {
-                    len = min(kMaxListChunk, max(1, (rest - seen) / (2 * G)));
-                    c = (int)__hip_atomic_fetch_add(tk, (unsigned)len, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-                }
-                s_c = c;
-                s_len = len;
-            }
+            if (threadIdx.x == 0) s_c = (int)claimed;
             __syncthreads();
             const int c = __builtin_amdgcn_readfirstlane(s_c);
-            if (c >= rest) return;
-            const int e = min(rest, c + __builtin_amdgcn_readfirstlane(s_len));
-            for (int it = G + c; it < G + e; ++it) visit(it);
+            if (c >= n) return;
+            const int e = min(n, c + len);
+            len = chunk(e);
+            claim(len);
+            for (int i = c; i < e; ++i) visit(G + g + P * i);
         }
     }
     const int per_range = max(1, G / kRanges);
     const int home = (int)(blockIdx.x % kRanges);
-    unsigned *tk = tv.ticket + t * kRanges;
+    unsigned *tks = tv.ticket + t * kClaims * kClaimStride;
     for (int p = 0; p < kRanges; ++p) {
         const int r = (home + p) % kRanges;
+        unsigned *tk = tks + r * kClaimStride;
         const int lo = (int)((long long)total * r / kRanges);
         const int n = (int)((long long)total * (r + 1) / kRanges) - lo;
         if (r < home) seg = 0;   // wrapped round to an earlier range
@@ -302,10 +316,10 @@ __device__ inline void for_each_item(const TabView &tv, int t, int sched, F &&bo
             if (threadIdx.x == 0) {
                 int c = n, len = 0;
                 const int seen =
-                    (int)__hip_atomic_load(tk + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    (int)__hip_atomic_load(tk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (seen < n) {
                     len = max(1, (n - seen) / (2 * per_range));
-                    c = (int)__hip_atomic_fetch_add(tk + r, (unsigned)len, __ATOMIC_RELAXED,
+                    c = (int)__hip_atomic_fetch_add(tk, (unsigned)len, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
                 }
                 s_c = c;
@@ -320,25 +334,31 @@ __device__ inline void for_each_item(const TabView &tv, int t, int sched, F &&bo
     }
 }
 
-// Takes the next ticket of list t for the block: returns false when the list is used up.
-// Used where items must be taken in order by running blocks (the MGS block groups).
-__device__ inline bool next_item(const TabView &tv, int t, int *slot_out, int *local_out)
+// Takes the block's next ticket of list t (turn: how many it took): returns false when the
+// list is used up. Used where items must be taken by running blocks (the MGS block groups).
+// A list no longer than the grid: block b takes item b and no other, without a claim; the
+// blocks of a group start in order, and a group that waits for blocks not yet started does
+// so beside groups that finish. A longer list: tickets in the order of the claims.
+__device__ inline bool next_item(const TabView &tv, int t, int turn, int *slot_out, int *local_out)
 {
     __shared__ int s_slot, s_local;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const unsigned it = __hip_atomic_fetch_add(tv.ticket + t * kRanges, 1u,
-                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int total = tv.total[t];
+        int it = turn == 0 ? (int)blockIdx.x : total;
+        if (total > (int)gridDim.x)
+            it = (int)__hip_atomic_fetch_add(tv.ticket + t * kClaims * kClaimStride, 1u, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
         int slot = -1, local = 0;
-        if ((int)it < tv.total[t]) {
+        if (it < total) {
             int lo = 0, hi = tv.nseg[t] - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (tv.seg_first(t, mid) <= (int)it) lo = mid;
+                if (tv.seg_first(t, mid) <= it) lo = mid;
                 else hi = mid - 1;
             }
             slot = tv.seg_slot(t, lo);
-            local = (int)it - tv.seg_first(t, lo);
+            local = it - tv.seg_first(t, lo);
         }
         s_slot = slot;
         s_local = local;
@@ -453,7 +473,7 @@ __global__ __launch_bounds__(kBlock) void bmgs_kernel(const BatchInst *__restric
     // counter (a large, mostly idle grid would otherwise queue on it)
     if ((int)blockIdx.x >= tv.total[t]) return;
     int slot, rank;
-    while (next_item(tv, t, &slot, &rank)) {
+    for (int turn = 0; next_item(tv, t, turn, &slot, &rank); ++turn) {
         const BatchInst &d = D[slot];
         DevState *st = S + slot;
         const int k = st->kcur;
@@ -1256,7 +1276,7 @@ int engine_create(abg_precision p, int max_slots, hipStream_t s, Engine **out)
     if (hipStreamCreateWithFlags(&e->cap_stream2, hipStreamNonBlocking) != hipSuccess) return bad();
     if (hipEventCreateWithFlags(&e->fork_ev, hipEventDisableTiming) != hipSuccess) return bad();
     if (hipEventCreateWithFlags(&e->join_ev, hipEventDisableTiming) != hipSuccess) return bad();
-    const size_t tab_ints = (2 + kRanges) * kNumTab + 2 * (size_t)kNumTab * max_slots;
+    const size_t tab_ints = (2 + kClaims * kClaimStride) * kNumTab + 2 * (size_t)kNumTab * max_slots;
     if (hipMalloc(&e->d_desc, sizeof(BatchInst) * max_slots) != hipSuccess) return bad();
     if (hipMalloc(&e->d_st, sizeof(DevState) * max_slots) != hipSuccess) return bad();
     if (hipMalloc(&e->d_tab, sizeof(int) * tab_ints) != hipSuccess) return bad();
@@ -1266,7 +1286,7 @@ int engine_create(abg_precision p, int max_slots, hipStream_t s, Engine **out)
     e->tv.nseg = e->d_tab;
     e->tv.total = e->d_tab + kNumTab;
     e->tv.ticket = reinterpret_cast<unsigned *>(e->d_tab + 2 * kNumTab);
-    e->tv.slot = e->d_tab + (2 + kRanges) * kNumTab;
+    e->tv.slot = e->d_tab + (2 + kClaims * kClaimStride) * kNumTab;
     e->tv.first = e->tv.slot + (size_t)kNumTab * max_slots;
     e->tv.max_slots = max_slots;
     // every slot starts idle: zero scalars and descriptors

@@ -450,3 +450,22 @@ def test_orthogonalisation_at_group_edges(gpu_lib, method, N, n_ang, n_det):
     assert r.k_done == s.k_done == 6
     assert np.allclose(r.ls_hist, s.ls_hist, rtol=1e-9, atol=0.0)
     gg.close()
+
+
+@pytest.mark.parametrize("method", ["ab", "ba"])
+def test_lists_longer_than_the_grid(gpu_lib, method):
+    """Twelve problems of 256^2 x 360 angles: their forward (6480) and back (3072) items
+    outnumber the resident blocks three times, so most are claimed. Every problem's iterate
+    after two steps equals its iterate alone, bit for bit."""
+    import torch
+    abg = gpu_lib
+    gg = abg.Geometry(256, 360, 363)
+    rng = np.random.default_rng(13)
+    bs = [torch.tensor(rng.uniform(size=360 * 363), dtype=torch.float32, device="cuda") for _ in range(12)]
+    prob = lambda i: abg.Problem(g=gg, method=method, b=bs[i], k_max=2, stop="none", tag=i)
+    eng = abg.Engine(proj="f32", basis="f32", max_slots=12)
+    out = eng.run([prob(i) for i in range(12)])
+    for i in (0, 5, 11):
+        alone = abg.Engine(proj="f32", basis="f32", max_slots=1).run([prob(i)])[0]
+        assert torch.equal(alone.x, out[i].x), i
+    gg.close()
