@@ -123,7 +123,8 @@ struct MgsLaunch {
     double *hcol;                // out: k+1 values h_{1,k}..h_{k+1,k}
     void *vout;                  // out: w_{k+1} (tv), at V + k*ldv
     void *cur;                   // out: w_{k+1} converted back to tx
-    double *partials;            // reduction slot tables: 2 x rows x G doubles
+    double *partials;            // two reduction slot tables of rows x G doubles each
+    size_t table;                // distance of the two in doubles (>= rows x G)
     int rows;                    // rows per table (>= k + 3 for every step of the solve)
     unsigned *ticket;            // zeroed counter of this step: hands out block ranks
     double *q64;                 // FP64 scratch of L elements (needed when L > kRegMaxL)

@@ -83,6 +83,7 @@ struct BatchInst {
     unsigned *count;
     double bd_rel;
     int mgs_rows;
+    long long mgs_table;
     int need_res;
     int mgs_G, mgs_class;   // register tile class 0 small, 1 large, 3 huge; 2 streaming
     int chunk, n_chunks;
@@ -489,6 +490,7 @@ __global__ __launch_bounds__(kBlock) void bmgs_kernel(const BatchInst *__restric
         a.cur = gfield<TX>(d.cur);
         a.partials = gfield<double>(d.mgs_part);
         a.rows = d.mgs_rows;
+        a.table = (size_t)d.mgs_table;
         a.st = st;
         a.bd_rel = d.bd_rel;
         a.step = k;
@@ -954,6 +956,7 @@ struct Engine {
         d.q64 = v.q64;
         d.gram = v.gram;
         d.mgs_rows = v.mgs_rows;
+        d.mgs_table = v.mgs_part_cap / 2;
         d.count = v.count;
         d.bd_rel = (p.basis == ABG_F64 && p.proj == ABG_F64) ? 1e-14 : 1e-6;
         d.need_res = r.stop.kind == ABG_STOP_DP;

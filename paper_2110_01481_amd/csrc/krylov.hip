@@ -452,6 +452,7 @@ hipError_t launch_mgs(const MgsLaunch &m, hipStream_t s)
     d.cur = m.cur;
     d.partials = m.partials;
     d.rows = m.rows;
+    d.table = m.table;
     d.ticket = m.ticket;
     d.q64 = m.q64;
     d.st = m.st;

@@ -276,7 +276,9 @@ __device__ inline void gather_rows(const double *tab, int G, int R, double (*red
 // once, and every inner product is one group reduction in a fixed order. Writes
 // h_{1,k}..h_{k+1,k}, w_{k+1} (basis dtype) and its copy in q's dtype.
 //
-// Reduction slots: two tables (step parity) of `rows` rows x G doubles; step k uses
+// Reduction slots: two tables (step parity) of `rows` rows x G doubles, `table` doubles
+// apart whatever G is (step 0 and the later steps of a batched solve run with different
+// groups, and a group must not find another's partials in its own table); step k uses
 // table k & 1, row i for <q, w_i>, row k for ||q||^2 after the sweep and row k + 1 for
 // ||q_k||^2 before it. Each rank clears its own column of the other table (rows up to
 // k + 2) for the next step; both tables start cleared.
@@ -298,6 +300,7 @@ struct MgsDev {
     void *vout;
     void *cur;
     double *partials;
+    size_t table;
     int rows;
     unsigned *ticket;
     DevState *st;
@@ -790,8 +793,8 @@ __device__ inline void mgs_body(const MgsDev &a, int rank, int G, double *lds,
     TV wv[EW];
 #pragma unroll
     for (int e = 0; e < E; ++e) qv[e] = to_f64(q[e * kBlock]);
-    double *tab = a.partials + (size_t)(a.step & 1) * a.rows * G;
-    double *next = a.partials + (size_t)((a.step + 1) & 1) * a.rows * G;
+    double *tab = a.partials + (size_t)(a.step & 1) * a.table;
+    double *next = a.partials + (size_t)((a.step + 1) & 1) * a.table;
     // rows the next step uses: up to 2(k+1) in the low-synchronisation form
     const bool icwy = a.gram && il && a.k >= 2 && a.k <= kIcwyMaxK;
     const int clear_to = a.gram ? 2 * a.k + 2 : a.k + 2;
@@ -905,8 +908,8 @@ __device__ inline void mgs_stream_body(const MgsDev &a, int rank, int G, double 
     const TX *q = static_cast<const TX *>(a.q);
     const TV *V = static_cast<const TV *>(a.V);
     int *err = &a.st->error;
-    double *tab = a.partials + (size_t)(a.step & 1) * a.rows * G;
-    double *next = a.partials + (size_t)((a.step + 1) & 1) * a.rows * G;
+    double *tab = a.partials + (size_t)(a.step & 1) * a.table;
+    double *next = a.partials + (size_t)((a.step + 1) & 1) * a.table;
     if (threadIdx.x == 0) {
         const double empty = __longlong_as_double((long long)kSlotEmpty);
         for (int r = 0; r <= a.k + 2 && r < a.rows; ++r)

@@ -307,6 +307,7 @@ struct Solve {
         M.vout = vec(k);
         M.cur = cur;
         M.rows = ly.mgs_rows;
+        M.table = (size_t)ly.mgs_cap / 2;
         M.ticket = tick + k;
         M.q64 = q64;
         M.gram = gram;
