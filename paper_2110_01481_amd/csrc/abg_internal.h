@@ -126,7 +126,6 @@ struct MgsLaunch {
     double *partials;            // two reduction slot tables of rows x G doubles each
     size_t table;                // distance of the two in doubles (>= rows x G)
     int rows;                    // rows per table (>= k + 3 for every step of the solve)
-    unsigned *ticket;            // zeroed counter of this step: hands out block ranks
     double *q64;                 // FP64 scratch of L elements (needed when L > kRegMaxL)
     DevState *st;
     double bd_rel;               // breakdown: h_{k+1,k} <= bd_rel * ||q_k||

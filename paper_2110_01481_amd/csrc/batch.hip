@@ -494,7 +494,6 @@ __global__ __launch_bounds__(kBlock) void bmgs_kernel(const BatchInst *__restric
         a.st = st;
         a.bd_rel = d.bd_rel;
         a.step = k;
-        a.ticket = nullptr;
         a.q64 = gfield<double>(d.q64);
         a.set_beta = 0;
         a.giv = GivensDev{gfield<double>(d.H),

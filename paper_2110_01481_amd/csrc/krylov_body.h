@@ -302,7 +302,6 @@ struct MgsDev {
     double *partials;
     size_t table;
     int rows;
-    unsigned *ticket;
     DevState *st;
     double bd_rel;
     int step;

@@ -26,7 +26,7 @@ namespace {
 
 struct Layout {
     size_t V, Z, cur, q, rb0, tm, tn, fpws, H, R, cs, sn, g, Y, rho;
-    size_t part, mgs_part, tick, count, st, ncp, q64, gram, total;
+    size_t part, mgs_part, count, st, ncp, q64, gram, total;
     long long L, ldv, mp, np;
     int mgs_rows;
     long long mgs_cap;
@@ -72,7 +72,6 @@ Layout make_layout(const Geometry &g, int method, int k_max, abg_precision p, ab
     const long long gmax = std::min<long long>(kMaxGrid, (ly.L + 255) / 256);
     ly.mgs_cap = 2LL * ly.mgs_rows * gmax;
     ly.mgs_part = take((size_t)ly.mgs_cap * 8);
-    ly.tick = take((ld + 2) * 4);
     ly.q64 = ly.L > kRegMaxL ? take((size_t)ly.ldv * 8) : 0;
     ly.gram = take(gram_entries(k_max) * 8);
     ly.count = take(64);
@@ -229,7 +228,7 @@ struct Solve {
     char *W;
     void *V, *Z, *cur, *q, *rb0, *tm, *tn, *fpws;
     double *H, *R, *cs, *sn, *gv, *Y, *rho, *part, *mgs_part, *q64, *gram;
-    unsigned *count, *tick;
+    unsigned *count;
     DevState *dst;
     double *ncp;
     HostLease lease;
@@ -263,7 +262,6 @@ struct Solve {
         part = reinterpret_cast<double *>(W + ly.part);
         mgs_part = reinterpret_cast<double *>(W + ly.mgs_part);
         count = reinterpret_cast<unsigned *>(W + ly.count);
-        tick = reinterpret_cast<unsigned *>(W + ly.tick);
         q64 = ly.q64 ? reinterpret_cast<double *>(W + ly.q64) : nullptr;
         gram = reinterpret_cast<double *>(W + ly.gram);
         dst = reinterpret_cast<DevState *>(W + ly.st);
@@ -308,7 +306,6 @@ struct Solve {
         M.cur = cur;
         M.rows = ly.mgs_rows;
         M.table = (size_t)ly.mgs_cap / 2;
-        M.ticket = tick + k;
         M.q64 = q64;
         M.gram = gram;
         return M;
@@ -414,7 +411,6 @@ struct Solve {
         auto words = [](size_t bytes) { return (unsigned long long)(bytes / 4); };
         const FillRange fr[] = {
             {mgs_part, nullptr, 2ull * ly.mgs_cap, 0, (unsigned)empty, (unsigned)(empty >> 32)},
-            {tick, nullptr, (unsigned long long)ld + 2, 0, 0u, 0u},
             {count, nullptr, 16, 0, 0u, 0u},
             {H, nullptr, 2ull * ld * k_max, 0, 0u, 0u},
             {gv, nullptr, 2ull * ld, 0, 0u, 0u},
