@@ -163,11 +163,9 @@ hipError_t launch_combine(int tout, const void *base, double base_coef, int tv, 
                           size_t ldv, int kk, const double *coef, double sgn, void *out,
                           long long L, double *partials, unsigned *count, double *norm,
                           DevState *st, int k, hipStream_t s, DevState *snap = nullptr);
-// out = a - b with partial sums of out^2.
+// out = a - b and, with dst, dst = ||out|| (partials: one per block, count: zeroed counter).
 hipError_t launch_sub_norm(int t, const void *a, const void *b, void *out, long long L,
-                           double *partials, int *nblocks, hipStream_t s);
-// dst = sqrt(sum partials[0..nb)) (fixed order, one block).
-hipError_t launch_reduce_sqrt(const double *partials, int nb, double *dst, hipStream_t s);
+                           double *partials, unsigned *count, double *dst, hipStream_t s);
 // Givens update of column k of H, y_k into y (k entries), and rho = beta e_1 - H_k y_k
 // when rho is given (beta read on the device). `snap`: as for launch_combine.
 hipError_t launch_givens(double *H, int ld, double *R, double *cs, double *sn, double *g,

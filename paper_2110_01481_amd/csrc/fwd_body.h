@@ -29,15 +29,17 @@ __device__ inline int wave_max_i(int v)
     return v;
 }
 
-// Writes the zero-padded row-major copy xr (N x S, image column c at c + kPad) and the
+// Writes the padded row-major copy xr (N x S, image column c at c + kPad) and the
 // transposed copy xc (row c of xc = column c of the image), through a 32 x 33 LDS tile.
+// With `pads`, the tiles at the image's edges also zero the kPad columns on both sides of
+// their rows (a caller whose copies' padding is zero already leaves that out).
 template <typename T> struct PadLds {
     T tile[32][33];
 };
 template <typename T>
 __device__ inline void pad_transpose_tile(const T *__restrict__ x, T *__restrict__ xr,
                                           T *__restrict__ xc, int N, int S, int bx, int by,
-                                          PadLds<T> &lds)
+                                          PadLds<T> &lds, bool pads = false)
 {
     T (*tile)[33] = lds.tile;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
@@ -55,18 +57,13 @@ __device__ inline void pad_transpose_tile(const T *__restrict__ x, T *__restrict
         const int c = bx + j, r = by + tx;
         if (c < N && r < N) xc[(size_t)c * S + r + kPad] = tile[tx][j];
     }
-}
-
-// Zeroes the kPad columns on both sides of the 2N padded rows of xr and xc.
-template <typename T>
-__device__ inline void pad_zero_item(T *__restrict__ xr, T *__restrict__ xc, int N, int S, int idx)
-{
-    const int per_row = 2 * kPad;
-    if (idx >= 2 * N * per_row) return;
-    const int row = idx / per_row, e = idx % per_row;
-    const int col = e < kPad ? e : N + e;   // [0,kPad) and [N+kPad, N+2kPad)
-    T *base = row < N ? xr + (size_t)row * S : xc + (size_t)(row - N) * S;
-    base[col] = T(0);
+    if (pads) {
+        static_assert(kPad == 4, "two sides of 32 rows of four columns: 256 threads");
+        const int j = (threadIdx.x >> 2) & 31, right = threadIdx.x >> 7;
+        const int col = (threadIdx.x & 3) + (right ? N + kPad : 0);
+        if ((right ? bx + 32 >= N : bx == 0) && by + j < N) xr[(size_t)(by + j) * S + col] = T(0);
+        if ((right ? by + 32 >= N : by == 0) && bx + j < N) xc[(size_t)(bx + j) * S + col] = T(0);
+    }
 }
 
 // Bands of a forward walk are taken in groups of kChunk consecutive bands that start at a

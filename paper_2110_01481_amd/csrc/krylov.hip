@@ -235,30 +235,45 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(const TB *__restrict__ 
     }
 }
 
+// out = a - b and, with dst, dst = ||a - b||: the blocks' partials are added in block order by
+// the last block to finish (a launch of its own for that sum cost 4 us of each residual).
 template <typename T>
-__global__ __launch_bounds__(kBlock) void sub_norm_kernel(const T *__restrict__ a, const T *__restrict__ b,
-                                                          T *__restrict__ out, long long L,
-                                                          double *partials)
+__global__ __launch_bounds__(kBlock) void sub_norm_kernel(const T *a, const T *b, T *out, long long L,
+                                                          double *partials, unsigned *count, double *dst)
 {
     __shared__ double lds[kWaves];
-    const long long T_ = (long long)gridDim.x * kBlock;
+    __shared__ int last;
+    constexpr int kTrip = kCombU * kBlock;
     double ss = 0.0;
-    for (long long l = (long long)blockIdx.x * kBlock + threadIdx.x; l < L; l += T_) {
-        const double v = (double)a[l] - (double)b[l];
-        out[l] = (T)v;
-        ss = fma(v, v, ss);
+    for (long long l0 = (long long)blockIdx.x * kTrip + threadIdx.x; l0 < L; l0 += (long long)gridDim.x * kTrip) {
+        double v[kCombU];
+#pragma unroll
+        for (int u = 0; u < kCombU; ++u) {
+            const long long l = l0 + u * kBlock;
+            v[u] = l < L ? (double)a[l] - (double)b[l] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < kCombU; ++u) {
+            const long long l = l0 + u * kBlock;
+            if (l < L) out[l] = (T)v[u];
+            ss = fma(v[u], v[u], ss);
+        }
     }
+    if (!dst) return;
     ss = block_sum(ss, lds);
-    if (threadIdx.x == 0) partials[blockIdx.x] = ss;
-}
-
-__global__ __launch_bounds__(kBlock) void reduce_sqrt_kernel(const double *partials, int nb, double *dst)
-{
-    __shared__ double lds[kWaves];
-    double s = 0.0;
-    for (int j = threadIdx.x; j < nb; j += kBlock) s += partials[j];
-    s = block_sum(s, lds);
-    if (threadIdx.x == 0) *dst = sqrt(s);
+    if (threadIdx.x == 0) {
+        agent_store(partials + blockIdx.x, ss);
+        last = count_in(count, gridDim.x);
+    }
+    __syncthreads();
+    if (!last) return;
+    double t = 0.0;
+    for (int j = threadIdx.x; j < (int)gridDim.x; j += kBlock) t += agent_load(partials + j);
+    t = block_sum(t, lds);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *dst = sqrt(t);
+    }
 }
 
 template <typename T>
@@ -493,22 +508,15 @@ hipError_t launch_combine(int tout, const void *base, double base_coef, int tv, 
 }
 
 hipError_t launch_sub_norm(int t, const void *a, const void *b, void *out, long long L,
-                           double *partials, int *nblocks, hipStream_t s)
+                           double *partials, unsigned *count, double *dst, hipStream_t s)
 {
-    const int nb = blocks_for(L);
-    *nblocks = nb;
+    const int nb = blocks_for((L + kCombU - 1) / kCombU, 512);
     if (t == ABG_F64)
         sub_norm_kernel<double><<<nb, kBlock, 0, s>>>(static_cast<const double *>(a), static_cast<const double *>(b),
-                                                      static_cast<double *>(out), L, partials);
+                                                      static_cast<double *>(out), L, partials, count, dst);
     else
         sub_norm_kernel<float><<<nb, kBlock, 0, s>>>(static_cast<const float *>(a), static_cast<const float *>(b),
-                                                     static_cast<float *>(out), L, partials);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_sqrt(const double *partials, int nb, double *dst, hipStream_t s)
-{
-    reduce_sqrt_kernel<<<1, kBlock, 0, s>>>(partials, nb, dst);
+                                                     static_cast<float *>(out), L, partials, count, dst);
     return hipGetLastError();
 }
 

@@ -33,19 +33,11 @@ template <typename T>
 __global__ __launch_bounds__(256) void pad_transpose_kernel(const T *__restrict__ x,
                                                             T *__restrict__ xr,
                                                             T *__restrict__ xc, int N, int S,
-                                                            const DevState *st, int k)
+                                                            bool pads, const DevState *st, int k)
 {
     __shared__ PadLds<T> lds;
     if (halted(st, k)) return;
-    pad_transpose_tile(x, xr, xc, N, S, blockIdx.x * 32, blockIdx.y * 32, lds);
-}
-
-template <typename T>
-__global__ void pad_zero_kernel(T *__restrict__ xr, T *__restrict__ xc, int N, int S,
-                                const DevState *st, int k)
-{
-    if (halted(st, k)) return;
-    pad_zero_item(xr, xc, N, S, blockIdx.x * blockDim.x + threadIdx.x);
+    pad_transpose_tile(x, xr, xc, N, S, blockIdx.x * 32, blockIdx.y * 32, lds, pads);
 }
 
 // Block shape of the forward projectors: a block's four waves take 2^lg_apb consecutive
@@ -212,11 +204,8 @@ hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStr
     T *xc = xr + (size_t)N * S;
     if (x) {
         dim3 tgrid((N + 31) / 32, (N + 31) / 32);
-        pad_transpose_kernel<T><<<tgrid, 256, 0, s>>>(static_cast<const T *>(x), xr, xc, N, S, st, k);
-        if (!pads_zero) {
-            const int npad = 2 * N * 2 * kPad;
-            pad_zero_kernel<T><<<(npad + 255) / 256, 256, 0, s>>>(xr, xc, N, S, st, k);
-        }
+        pad_transpose_kernel<T><<<tgrid, 256, 0, s>>>(static_cast<const T *>(x), xr, xc, N, S, !pads_zero, st,
+                                                      k);
     }
     const FwdPlan plan = fwd_plan(g, sizeof(T) == 8 ? ABG_F64 : ABG_F32);
     const double s0 = -0.5 * (g.n_det - 1) * g.ds;

@@ -391,9 +391,7 @@ struct Solve {
     int literal_residual(const void *b, const void *x, double *out = nullptr)
     {
         RC(fwd(x, tm));
-        int nb = 0;
-        CK(launch_sub_norm(p.proj, b, tm, tm, g.m(), part, &nb, s));
-        CK(launch_reduce_sqrt(part, nb, out ? out : &dst->res, s));
+        CK(launch_sub_norm(p.proj, b, tm, tm, g.m(), part, count, out ? out : &dst->res, s));
         return ABG_OK;
     }
 
@@ -422,8 +420,7 @@ struct Solve {
         CK(launch_init_fill(fr, (int)(sizeof fr / sizeof fr[0]), &init, dst, s));
         if (x0) {
             RC(fwd(x0, tm));
-            int nb = 0;
-            CK(launch_sub_norm(p.proj, b, tm, rb0, m, part, &nb, s));
+            CK(launch_sub_norm(p.proj, b, tm, rb0, m, part, count, nullptr, s));
         }
         const void *r0 = rb0;
         if (method == ABG_METHOD_BA) {
@@ -699,9 +696,7 @@ int gmres_error_history(const Geometry &g, int method, int kind, int k_max, abg_
     for (int k = 1; k <= k_done; ++k) {
         // x_k into tn, then ||x_k - x_ref|| into host slot k
         RC(S.build_x(S.ycol(k), k, x0, S.tn));
-        int nb = 0;
-        CK(launch_sub_norm(p.proj, x_ref, S.tn, S.tn, n, S.part, &nb, s));
-        CK(launch_reduce_sqrt(S.part, nb, &S.hr.dslots[k].err, s));
+        CK(launch_sub_norm(p.proj, x_ref, S.tn, S.tn, n, S.part, S.count, &S.hr.dslots[k].err, s));
     }
     CK(hipStreamSynchronize(s));
     for (int k = 1; k <= k_done; ++k) err[k - 1] = S.hr.slots[k].err;
@@ -831,8 +826,7 @@ int run_lsq(const Geometry &g, int method, const void *b, const void *x0, void *
     }
     if (x0) {
         CK(launch_forward(g, dtype, x0, t, fpws, s, nullptr, 0, true));
-        int nb = 0;
-        CK(launch_sub_norm(dtype, b, t, t, m, part, &nb, s));
+        CK(launch_sub_norm(dtype, b, t, t, m, part, count, nullptr, s));
         if (lsmr) CK(hipMemcpyAsync(r, t, (size_t)m * sx, hipMemcpyDeviceToDevice, s));
     }
     // beta_1 u_1 = b - A x0, alpha_1 v_1 = A^T u_1, v_1, w_1 / h_1 and the scalars
@@ -857,17 +851,13 @@ int run_lsq(const Geometry &g, int method, const void *b, const void *x0, void *
         if (ncp_stop) {
             // the NCP distance of the explicit residual b - A x_k (its norm into res)
             CK(launch_forward(g, dtype, x, tres, fpws, s, dst, k, true));
-            int nb = 0;
-            CK(launch_sub_norm(dtype, b, tres, tres, m, part, &nb, s));
-            CK(launch_reduce_sqrt(part, nb, &dst->res, s));
+            CK(launch_sub_norm(dtype, b, tres, tres, m, part, count, &dst->res, s));
             CK(launch_ncp(g, dtype, tres, ncp, dst, k, s, hr.dslots + k));
         }
         if (x_ref) {
             // ||x_k - x_ref|| into slot k, after the step's copy of the scalars (sv is
             // free until the next step's back projection)
-            int nb = 0;
-            CK(launch_sub_norm(dtype, x_ref, x, sv, n, part, &nb, s));
-            CK(launch_reduce_sqrt(part, nb, &hr.dslots[k].err, s));
+            CK(launch_sub_norm(dtype, x_ref, x, sv, n, part, count, &hr.dslots[k].err, s));
         }
         CK(hipEventRecord(hr.ev[k % kRing], s));
         return ABG_OK;
@@ -881,9 +871,7 @@ int run_lsq(const Geometry &g, int method, const void *b, const void *x0, void *
     // ||b - A x|| into dst->res
     auto literal_residual = [&]() -> int {
         CK(launch_forward(g, dtype, x, tres, fpws, s, nullptr, 0, true));
-        int nb = 0;
-        CK(launch_sub_norm(dtype, b, tres, tres, m, part, &nb, s));
-        CK(launch_reduce_sqrt(part, nb, &dst->res, s));
+        CK(launch_sub_norm(dtype, b, tres, tres, m, part, count, &dst->res, s));
         return ABG_OK;
     };
     auto hist = [&](double *arr, int k, double val) {

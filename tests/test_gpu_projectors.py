@@ -284,3 +284,26 @@ def test_config3_sampled_f32(gpu_lib):
     ones = torch.ones(gg.m, dtype=torch.float32, device="cuda")
     xb = gg.bp(ones, "hat")
     assert float((xb - w.n_ang).abs().max()) <= 1e-5 * w.n_ang
+
+
+@pytest.mark.parametrize("N", [1, 31, 32, 33, 64])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_forward_scratch_contents_do_not_matter(gpu_lib, N, dt):
+    """The padding of the scratch copies is written with them, in the tiles at the image's
+    edges: A x over a scratch full of NaN equals A x over a scratch of zeros, bit for bit, at
+    images below, at and past a tile's size, for the line and the strip model (whose taps
+    reach furthest past the edge)."""
+    import torch
+    abg = gpu_lib
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    x = torch.tensor(np.random.default_rng(3).uniform(size=N * N), dtype=tdt, device="cuda")
+    for model in ("line", "strip"):
+        gg = abg.Geometry(N, 24, 2 * N + 3, model=model)
+        gg.fp(x)
+        (ws,) = gg._fp_ws.values()
+        ws.fill_(0)
+        want = gg.fp(x).clone()
+        ws.fill_(255)
+        got = gg.fp(x)
+        assert torch.equal(got, want) and bool(torch.isfinite(got).all())
+        gg.close()
