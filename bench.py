@@ -32,20 +32,21 @@ HBM_PEAK_GBPS = 8000.0
 PROFILES = os.path.join(ROOT, "profiles")
 _CSRC = "paper_2110_01481_amd/csrc/"
 # kernels whose stored counter summaries (profiles/<kernel>_<workload>_counters.md) bench.py
-# reads: the kernel-name prefix in rocprofv3's CSV and the sources whose change makes the
-# stored readings stale
+# reads: the kernel-name prefixes in rocprofv3's CSV (the launches a projection may take)
+# and the sources whose change makes the stored readings stale
+_FWD_SRC = [_CSRC + "fwd_body.h", _CSRC + "footprint.h", _CSRC + "geometry.h", _CSRC + "projectors.hip"]
+_BACK_SRC = [_CSRC + "back_body.h", _CSRC + "back_orbit.h", _CSRC + "footprint.h", _CSRC + "geometry.h",
+             _CSRC + "projectors.hip"]
 COUNTER_KERNELS = {
-    "forward_kernel_f32": ("forward_kernel<float>",
-                           [_CSRC + "fwd_body.h", _CSRC + "geometry.h", _CSRC + "projectors.hip"]),
-    "forward_kernel_f64": ("forward_kernel<double>",
-                           [_CSRC + "fwd_body.h", _CSRC + "geometry.h", _CSRC + "projectors.hip"]),
-    "back_kernel_f64": ("back_kernel<double, false, false, true>",
-                        [_CSRC + "back_body.h", _CSRC + "geometry.h", _CSRC + "projectors.hip"]),
-    "back_kernel_f32": ("back_kernel<float, false, false, true>",
-                        [_CSRC + "back_body.h", _CSRC + "geometry.h", _CSRC + "projectors.hip"]),
+    "forward_kernel_f32": (("forward_staged_kernel<float", "forward_kernel<float"), _FWD_SRC),
+    "forward_kernel_f64": (("forward_staged_kernel<double", "forward_kernel<double"), _FWD_SRC),
+    "back_kernel_f64": (("back_orbit_kernel<double, 0, 8, false>", "back_orbit_kernel<double, 0, 16, false>",
+                         "back_kernel<double, false, false, true>"), _BACK_SRC),
+    "back_kernel_f32": (("back_orbit_kernel<float, 0, 8, false>", "back_orbit_kernel<float, 0, 16, false>",
+                         "back_kernel<float, false, false, true>"), _BACK_SRC),
 }
 # kernels of a solve whose L2 hit rate the TCC pass reports
-L2_KERNELS = ("forward_kernel", "back_kernel", "mgs_kernel", "mgs_stream_kernel",
+L2_KERNELS = ("forward_staged_kernel", "forward_kernel", "back_orbit_kernel", "back_kernel", "mgs_kernel", "mgs_stream_kernel",
               "combine_kernel", "ncp_fft_rows_kernel", "ncp_colsum_kernel")
 
 
@@ -67,7 +68,7 @@ def forward_source_hash() -> str:
     return source_hash("forward_kernel_f32")
 
 
-def _counter_means(csv_path: str, kernel_prefix: str) -> dict:
+def _counter_means(csv_path: str, kernel_prefix) -> dict:
     import csv
     sums, counts = {}, {}
     with open(csv_path) as fh:
@@ -86,9 +87,10 @@ def summarize_counters(d: str, kernel_key: str = "forward_kernel_f32",
     """Markdown summary of the FETCH_SIZE / WRITE_SIZE passes under directory d (sub-
     directories fetch, write, cfetch, cwrite, and optionally sq and l2, as written by the
     commands listed in it) for the kernel `kernel_key` of COUNTER_KERNELS."""
-    kname = COUNTER_KERNELS[kernel_key][0]
-    f = _counter_means(os.path.join(d, "fetch", "run_counter_collection.csv"), kname)
-    w = _counter_means(os.path.join(d, "write", "run_counter_collection.csv"), kname)
+    prefixes = COUNTER_KERNELS[kernel_key][0]
+    kname = " / ".join(prefixes)
+    f = _counter_means(os.path.join(d, "fetch", "run_counter_collection.csv"), prefixes)
+    w = _counter_means(os.path.join(d, "write", "run_counter_collection.csv"), prefixes)
     cf = _counter_means(os.path.join(d, "cfetch", "run_counter_collection.csv"), "__amd_rocclr_copyBuffer")
     cw = _counter_means(os.path.join(d, "cwrite", "run_counter_collection.csv"), "__amd_rocclr_copyBuffer")
     copy_kib = 1024 * 1024
@@ -104,7 +106,7 @@ def summarize_counters(d: str, kernel_key: str = "forward_kernel_f32",
                                                    data["write_kib_per_dispatch"] * data["write_scale"]))
     sq_csv = os.path.join(d, "sq", "run_counter_collection.csv")
     if os.path.exists(sq_csv):
-        sq = _counter_means(sq_csv, kname)
+        sq = _counter_means(sq_csv, prefixes)
         data["valu_wave_insts_per_dispatch"] = round(sq["SQ_INSTS_VALU"], 1)
         if "SQ_INSTS_VMEM_RD" in sq:
             data["vmem_read_wave_insts_per_dispatch"] = round(sq["SQ_INSTS_VMEM_RD"], 1)
@@ -125,7 +127,7 @@ def summarize_counters(d: str, kernel_key: str = "forward_kernel_f32",
         f"# HBM traffic of {kname} ({workload})",
         "",
         f"Counters per dispatch of `{kname}`, averaged over the dispatches of the",
-        "run, and of the plain device copy of 1 GiB (`__amd_rocclr_copyBuffer`) that calibrates",
+        "run that match, and of the plain device copy of 1 GiB (`__amd_rocclr_copyBuffer`) that calibrates",
         "them: the copy reads and writes exactly 1 GiB, so each counter is scaled by",
         "1 GiB / (its reading on the copy).",
         "",
@@ -841,9 +843,9 @@ def roofline_of(prof, w, proj: str, tag: str):
     avg_ms = ms / n
     peak = FP64_VECTOR_PEAK_TFLOPS if proj == "f64" else FP32_VECTOR_PEAK_TFLOPS
     work, _ = _work_per_launch(w, proj)
-    names = {"forward": f"forward_kernel<{'double' if proj == 'f64' else 'float'}> (ray-driven "
+    names = {"forward": f"forward_staged_kernel<{'double' if proj == 'f64' else 'float'}> (ray-driven "
                         f"line model A, {proj.upper()})",
-             "back": f"back_kernel (pixel-driven unmatched B, {proj.upper()})",
+             "back": f"back_orbit_kernel (pixel-driven unmatched B, {proj.upper()})",
              "ncp": "ncp_fft_rows/colsum/dist/final kernels (periodogram of every sinogram row, FP64)",
              "mgs": "mgs kernels (Gram-Schmidt + Givens)", "combine": "combine_kernel"}
     roof = {"kernel": names[dominant], "avg_launch_ms": round(avg_ms, 4),
@@ -866,17 +868,8 @@ def roofline_of(prof, w, proj: str, tag: str):
                 lane_ops = 64.0 * tr["valu_wave_insts_per_dispatch"]
                 roof["valu_issue_frac"] = round(lane_ops / (avg_ms * 1e-3) / VALU_ISSUE_PEAK, 4)
             if tr.get("l2_hit_rate"):
-                roof["l2_hit_rate"] = tr["l2_hit_rate"].get(dominant + "_kernel")
-            if dominant == "forward" and "vmem_read_wave_insts_per_dispatch" in tr:
-                # the forward walk issues one 64-lane gather per band and wave: its issue
-                # rate per CU, in cycles of the 2.4 GHz peak clock (a texture path taking
-                # four lane addresses per cycle needs 16)
-                g = tr["vmem_read_wave_insts_per_dispatch"]
-                roof["gathers"] = {
-                    "wave_gathers_per_launch": int(g),
-                    "cycles_per_gather_per_cu_at_2_4_ghz": round(avg_ms * 1e-3 * 2.4e9 / (g / 256), 1),
-                    "note": "one 64-lane gather per band and wave; 16 cycles each at four lane "
-                            "addresses per cycle"}
+                l2 = {"forward": "forward_staged_kernel", "back": "back_orbit_kernel"}
+                roof["l2_hit_rate"] = tr["l2_hit_rate"].get(l2.get(dominant))
     else:
         roof.update({"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": None, "traffic": None})

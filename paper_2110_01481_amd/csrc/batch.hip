@@ -16,8 +16,8 @@
 // graph does not change while problems join and leave (two variants are kept: the AB and
 // BA projector chains in sequence, or as two branches while the problems are small); it is
 // captured again when a problem first needs a list that no earlier one did. Rounds queue
-// behind one another without a host wait between them. Blocks take work items from a
-// per-list ticket counter; an item's arithmetic depends only on its own problem, so a
+// behind one another without a host wait between them. Blocks take work items in
+// list order; an item's arithmetic depends only on its own problem, so a
 // problem's results are the same alone and in any mix.
 //
 // The host reads a copy of the per-problem scalars one round behind. A DP candidate, a
@@ -209,20 +209,6 @@ __global__ __launch_bounds__(256) void begin_kernel(const BatchInst *__restrict_
         tv.total[t] = tot_c;
     }
     if (tid < kClaims) tv.ticket[(t * kClaims + tid) * kClaimStride] = 0u;
-}
-
-// Problem and item of ticket `it` of list t (binary search over the segments). Every
-// thread of a block calls it with the same ticket, so the loads are uniform.
-__device__ inline void locate(const TabView &tv, int t, int it, int *slot, int *local)
-{
-    int lo = 0, hi = tv.nseg[t] - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tv.seg_first(t, mid) <= it) lo = mid;
-        else hi = mid - 1;
-    }
-    *slot = __builtin_amdgcn_readfirstlane(tv.seg_slot(t, lo));
-    *local = __builtin_amdgcn_readfirstlane(it - tv.seg_first(t, lo));
 }
 
 // Runs body(slot, local) for the items of list t that this block takes, under one of three
