@@ -39,11 +39,10 @@
 namespace abg {
 
 // Work lists are split into kRanges contiguous ranges with a counter each (see
-// for_each_item); the list-order schedule claims at most kMaxListChunk items at a time.
+// for_each_item).
 constexpr int kRanges = 8;
 constexpr int kClaims = 32;        // claim counters of a list
 constexpr int kClaimStride = 32;   // their distance in words: one cache line
-constexpr int kMaxListChunk = 8;
 
 enum Tab {
     kTPadBA = 0,   // pad w_k (BA)
@@ -88,6 +87,7 @@ struct BatchInst {
     int mgs_G, mgs_class;   // register tile class 0 small, 1 large, 3 huge; 2 streaming
     int chunk, n_chunks;
     int fwd_rays;           // forward block shape of the single-solve rule (tiles.rays = 0)
+    FwdOrder fwd_order;     // four-angle forward items in tiles per XCD (rows > 0: large images)
 };
 
 // Work lists: list t holds segments (problem, first ticket); items of a segment are
@@ -115,6 +115,25 @@ namespace {
 
 __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Forward items of four angles in tiles dealt out to the XCDs, as a single launch does above
+// N = 896. The static and the list-order schedules run item i of a list on XCD i mod 8
+// (blocks are dealt out so, and claims keep it); ranges per XCD (sched 1) take the plain order,
+// which keeps a range's items near one another. In list order the plain order made each XCD
+// read every image: four 2048^2 x 1800 problems, FP32, 12.1 ms per round, 9.1 in tiles.
+__device__ inline bool in_tiles(const BatchInst &d, const Tiles &tl, int rays)
+{
+    return rays == 64 && d.fwd_order.rows > 0 && tl.sched != 1;
+}
+// Ray group and angle group of forward item `local`: false for an item past the last.
+__device__ inline bool fwd_item(const BatchInst &d, const Tiles &tl, int rays, int local, int &gx, int &gy)
+{
+    if (in_tiles(d, tl, rays)) return d.fwd_order.block(local, gx, gy);
+    const int nrg = ceil_div(d.n_det, rays);
+    gy = local / nrg;
+    gx = local - gy * nrg;
+    return gy < ceil_div(d.n_ang, 256 / rays);
+}
+
 __device__ int items_of(int t, const BatchInst &d, const Tiles &tl)
 {
     const bool ba = d.method == ABG_METHOD_BA;
@@ -134,7 +153,9 @@ __device__ int items_of(int t, const BatchInst &d, const Tiles &tl)
     case kTFwdAB: {
         if ((t == kTFwdBA) != ba) return 0;
         const int rays = tl.rays ? tl.rays : d.fwd_rays;
-        return ceil_div(d.n_ang, 256 / rays) * ceil_div(d.n_det, rays);
+        // whole eights, so that item i of a problem runs on XCD i mod 8 (fwd_item)
+        if (in_tiles(d, tl, rays)) return (int)d.fwd_order.blocks();
+        return (ceil_div(d.n_ang, 256 / rays) * ceil_div(d.n_det, rays) + 7) & ~7;
     }
     case kTMgsS: return d.mgs_class == 0 ? d.mgs_G : 0;
     case kTMgsL: return d.mgs_class == 1 ? d.mgs_G : 0;
@@ -222,19 +243,17 @@ __global__ __launch_bounds__(256) void begin_kernel(const BatchInst *__restrict_
 //           guided: a claim takes half of what is left of the range divided by the blocks
 //           that start on it, so the last items go one at a time and a phase does not
 //           wait on one block's large final chunk (an item of a 2048^2 problem is ~0.1 ms).
-//  sched 2  list order: block b takes item b, then claims of the items after the first
-//           `grid`: those at distance g, g + kClaims, ... belong to the blocks b with
-//           b % kClaims = g, which share a counter (of its own cache line) and take them in
-//           guided chunks (what is left over twice the blocks, between 1 and kMaxListChunk).
-//           A block claims its next chunk before it works on the present one. (Claims take
-//           about 56 ns each on one counter of the whole list: with that, twelve problems
-//           of 256^2 x 360, FP32, took 370 us in the forward phase, 130 now, and 174 in the back
-//           projection, 76 now.) The running blocks all work on the same one or two
-//           problems, as the blocks of a single solve's launch do, so only those problems'
-//           images and sinograms compete for the caches (with one range per XCD, or with
-//           chunks of ~100 items, eight or more large problems are in flight at once, more
-//           than the Infinity Cache holds, and a served batch ran 15% slower); a list no
-//           longer than the grid takes no claim at all.
+//  sched 2  list order: block b takes item b, then claims items after the first `grid` one at
+//           a time: those at distance g, g + kClaims, ... belong to the blocks b with
+//           b % kClaims = g, which share a counter (of its own cache line). A block claims
+//           its next item before it works on the present one. (Claims on one counter of the
+//           whole list take about 56 ns each: with that, twelve problems of 256^2 x 360, FP32,
+//           took 370 us in the forward phase, 128 now, and 174 in the back projection, 73
+//           now.) The running blocks all work on the same one or two problems, as the blocks
+//           of a single solve's launch do, so only those problems' images and sinograms
+//           compete for the caches: claims of up to eight items at a time spread the blocks
+//           over eight times as many (eight problems of 1024^2 x 720: 2.9 ms forward, 1.75
+//           with single claims). A list no longer than the grid takes no claim at all.
 // The pad and residual lists (uniform, cheap items) always run sched 0.
 // A block's items come in increasing order, so the segment (problem) of an item is found
 // by moving a cursor forward. body must be called by the whole block (it may
@@ -265,17 +284,13 @@ __device__ inline void for_each_item(const TabView &tv, int t, int sched, F &&bo
         }
         const int P = min(kClaims, G), g = (int)blockIdx.x % P;
         const int n = (rest - g + P - 1) / P;         // this counter's items: G + g + P c, c < n
-        const int blocks = (G - g + P - 1) / P;       // that share it
         unsigned *tk = tv.ticket + (t * kClaims + g) * kClaimStride;
-        auto chunk = [&](int done) { return min(kMaxListChunk, max(1, (n - done) / (2 * blocks))); };
-        unsigned claimed = 0;                         // thread 0: the next chunk's first c
-        auto claim = [&](int len) {
+        unsigned claimed = 0;                         // thread 0: the next unit
+        auto claim = [&] {
             if (threadIdx.x == 0)
-                claimed = __hip_atomic_fetch_add(tk, (unsigned)len, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
+                claimed = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
-        int len = chunk(0);
-        claim(len);
+        claim();
         visit(blockIdx.x);
         for (;;) {
             __syncthreads();
@@ -283,10 +298,8 @@ __device__ inline void for_each_item(const TabView &tv, int t, int sched, F &&bo
             __syncthreads();
             const int c = __builtin_amdgcn_readfirstlane(s_c);
             if (c >= n) return;
-            const int e = min(n, c + len);
-            len = chunk(e);
-            claim(len);
-            for (int i = c; i < e; ++i) visit(G + g + P * i);
+            claim();
+            visit(G + g + P * c);
         }
     }
     const int per_range = max(1, G / kRanges);
@@ -398,20 +411,20 @@ __global__ __launch_bounds__(256, 8) void bfwd_kernel(const BatchInst *__restric
         const int rays = tl.rays ? tl.rays : d.fwd_rays;
         const int wpa = rays / 64;       // waves per angle
         const int apb = 256 / rays;      // angles per block
-        const int nrg = (d.n_det + rays - 1) / rays;
+        int gx, gy;
+        if (!fwd_item(d, tl, rays, local, gx, gy)) return;   // the whole block
         // four-angle items (or a forced share of them, spread by a hash of the item) walk with
         // their band rows staged in LDS (the whole block, before any wave leaves)
         if (rays == 64 && tl.stage > 0 &&
             (int)(((unsigned)local * 0x9E3779B1u + (unsigned)slot * 0x85EBCA6Bu) >> 29) < tl.stage) {
             T *y = mode == 0 ? zcol<T>(d, k) : gfield<T>(d.q);
             forward_block_staged<T, 4>(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
-                                       gfield<const AngleParams>(d.ang), (local / nrg) * 4,
-                                       (local % nrg) * 64, d.N, d.S, d.n_ang, d.n_det, d.ds, d.s0,
+                                       gfield<const AngleParams>(d.ang), gy * 4, gx * 64, d.N, d.S, d.n_ang, d.n_det, d.ds, d.s0,
                                        lds);
             return;
         }
-        const int a = (local / nrg) * apb + wave / wpa;
-        const int i = (local % nrg) * rays + (wave % wpa) * 64 + lane;
+        const int a = gy * apb + wave / wpa;
+        const int i = gx * rays + (wave % wpa) * 64 + lane;
         if (a >= d.n_ang) return;   // whole waves
         T *y = mode == 0 ? zcol<T>(d, k) : gfield<T>(d.q);
         forward_ray(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
@@ -947,6 +960,7 @@ struct Engine {
         d.need_res = r.stop.kind == ABG_STOP_DP;
         const FwdPlan fp = fwd_plan(g, p.proj);
         d.fwd_rays = fp.nw > 0 ? 64 : 256 >> fp.lg;
+        d.fwd_order = FwdOrder::make((g.n_det + 63) / 64, (g.n_ang + 3) / 4, fp.tiled);
         // Gram-Schmidt class: the smallest register tile whose block group the device
         // holds at once (the small tile while its group stays small), else the streaming
         // variant. A group must be resident as a whole: its size stays within the

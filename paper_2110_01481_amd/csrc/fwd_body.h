@@ -419,6 +419,41 @@ __device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict
     if (i < n_det) y[(size_t)a * n_det + i] = sum.times(P.len);
 }
 
+// Order of the blocks of a staged launch: ngx ray groups (64 rays) by ngy angle groups (NW
+// angles). With rows == 0 the ray group runs fastest. Otherwise the blocks come in tiles of
+// one ray group by `rows` angle groups, dealt out to the eight XCDs (blocks b with equal b
+// mod 8 run on one XCD), the ray group fastest within a row of tiles: the blocks an XCD
+// holds at one time then walk nearly the same image pixels, which stay in its 4 MB L2.
+// `cols`, the tiles of a row, is ngx padded to 2 mod 4: the XCDs move on by 2 or 6 ray
+// groups from one row of tiles to the next and so share long (central) and short rays
+// evenly over the kFwdTileRows rows. Tiles and blocks past the ends leave at once.
+constexpr int kFwdTileRows = 4;
+struct FwdOrder {
+    int ngx, ngy, rows, cols;
+    static FwdOrder make(int ngx, int ngy, bool tiled)
+    {
+        return tiled ? FwdOrder{ngx, ngy, (ngy + kFwdTileRows - 1) / kFwdTileRows, ngx + (6 - ngx % 4) % 4}
+                     : FwdOrder{ngx, ngy, 0, 0};
+    }
+    __host__ __device__ long long blocks() const
+    {
+        return rows == 0 ? (long long)ngx * ngy : ((long long)cols * kFwdTileRows + 7) / 8 * 8 * rows;
+    }
+    __device__ bool block(int b, int &gx, int &gy) const
+    {
+        if (rows == 0) {
+            gy = b / ngx;
+            gx = b - gy * ngx;
+            return true;
+        }
+        const int i = b >> 3, j = i / rows;
+        const int t = 8 * j + (b & 7), tr = t / cols;
+        gx = t - tr * cols;
+        gy = tr * rows + (i - j * rows);
+        return gx < ngx && gy < ngy;
+    }
+};
+
 // ---- several angles per block, band rows staged in LDS (line and Joseph models) -----------
 // The forward walk above issues one 64-lane gather per band and wave, and the texture
 // path takes them at four lane addresses per cycle: that rate bounds it. A block of four

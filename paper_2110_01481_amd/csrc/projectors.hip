@@ -56,32 +56,6 @@ struct FwdShape {
     }
 };
 
-// Order of the blocks of a staged launch: ngx ray groups (64 rays) by ngy angle groups (NW
-// angles). With rows == 0 the ray group runs fastest. Otherwise the blocks come in tiles of
-// one ray group by `rows` angle groups, dealt out to the eight XCDs (blocks b with equal b
-// mod 8 run on one XCD), the ray group fastest within a row of tiles: the blocks an XCD
-// holds at one time then walk nearly the same image pixels, which stay in its 4 MB L2.
-// `cols`, the tiles of a row, is ngx padded to 2 mod 4: the XCDs move on by 2 or 6 ray
-// groups from one row of tiles to the next and so share long (central) and short rays
-// evenly over the kFwdTileRows rows. Tiles and blocks past the ends leave at once.
-struct FwdOrder {
-    int ngx, ngy, rows, cols;
-    __device__ bool block(int b, int &gx, int &gy) const
-    {
-        if (rows == 0) {
-            gy = b / ngx;
-            gx = b - gy * ngx;
-            return true;
-        }
-        const int i = b >> 3, j = i / rows;
-        const int t = 8 * j + (b & 7), tr = t / cols;
-        gx = t - tr * cols;
-        gy = tr * rows + (i - j * rows);
-        return gx < ngx && gy < ngy;
-    }
-};
-constexpr int kFwdTileRows = 4;
-
 // Line and Joseph models, NW angles per block, band rows staged in LDS
 // (forward_block_staged): bound by
 // the VALU (8 instructions per band, wave and ray; 83% busy at 2048^2 x 1800 in FP64) beside
@@ -212,13 +186,8 @@ hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStr
     // timed at the kernel's own start and end when profiling is on
     ProfScope ps(kProfFwd, s, st ? k : 0, true);
     if (g.model != ABG_FP_STRIP && plan.nw > 0) {
-        FwdOrder ord{(g.n_det + 63) / 64, (g.n_ang + plan.nw - 1) / plan.nw, 0, 0};
-        size_t blocks = (size_t)ord.ngx * ord.ngy;
-        if (plan.tiled) {
-            ord.rows = (ord.ngy + kFwdTileRows - 1) / kFwdTileRows;
-            ord.cols = ord.ngx + (6 - ord.ngx % 4) % 4;
-            blocks = ((size_t)ord.cols * kFwdTileRows + 7) / 8 * 8 * ord.rows;
-        }
+        const FwdOrder ord = FwdOrder::make((g.n_det + 63) / 64, (g.n_ang + plan.nw - 1) / plan.nw, plan.tiled);
+        const size_t blocks = ord.blocks();
         auto pick = [&](auto model) {
             constexpr int M = decltype(model)::value;
             return plan.nw == 8 ? forward_staged_kernel<T, 8, M> : forward_staged_kernel<T, 4, M>;

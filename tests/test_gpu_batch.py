@@ -469,3 +469,25 @@ def test_lists_longer_than_the_grid(gpu_lib, method):
         alone = abg.Engine(proj="f32", basis="f32", max_slots=1).run([prob(i)])[0]
         assert torch.equal(alone.x, out[i].x), i
     gg.close()
+
+
+@pytest.mark.parametrize("method", ["ab", "ba"])
+def test_forward_items_in_tiles_per_xcd(gpu_lib, method):
+    """Above N = 896 the static and the list-order schedules take the forward items in tiles
+    dealt out to the XCDs, the ranges per XCD in plain order: two problems of ragged angle
+    and ray groups beside a small one give the same bits under all three."""
+    import torch
+    abg = gpu_lib
+    geoms = [abg.Geometry(897, 13, 1271), abg.Geometry(1000, 530, 1415), abg.Geometry(100, 37, 143)]
+    rng = np.random.default_rng(14)
+    bs = [torch.tensor(rng.uniform(size=g.m), dtype=torch.float32, device="cuda") for g in geoms]
+    outs = []
+    for sched in (0, 1, 2):
+        eng = abg.Engine(proj="f32", basis="f32", max_slots=3)
+        eng.set_tiles(64, 64, sched)
+        outs.append(eng.run([abg.Problem(g=g, method=method, b=b, k_max=2, stop="none", tag=i)
+                             for i, (g, b) in enumerate(zip(geoms, bs))]))
+    for o in outs[1:]:
+        assert all(torch.equal(a.x, b.x) for a, b in zip(outs[0], o))
+    for g in geoms:
+        g.close()
