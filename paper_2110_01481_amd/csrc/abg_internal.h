@@ -151,7 +151,12 @@ constexpr size_t gram_entries(int k_max)
     const size_t r = (size_t)(k_max < kIcwyMaxK ? k_max : kIcwyMaxK);
     return r * (r - 1) / 2 + 1;
 }
+// A launch of more than one block waits on the device for all of them: the caller holds the
+// share of the device that mgs_group_units names.
 hipError_t launch_mgs(const MgsLaunch &a, hipStream_t s);
+// Step 0 (k = 0) for a caller that holds no share: two launches, no block waits for another
+// (partials: one per block, up to 512; count: zeroed counter). Precisions of an engine.
+hipError_t launch_start(const MgsLaunch &a, double *partials, unsigned *count, hipStream_t s);
 
 // out = base_coef*base + sum_{j<kk} sgn*coef[j]*V_j  (FP64 accumulation). With `norm`
 // set, ||out||_2 is reduced in a fixed order by the last block to finish and written to

@@ -29,8 +29,8 @@ constexpr int kCombU = 4;
 constexpr int kCombJ = 8;   // basis columns per trip of the combination
 
 // Block b is rank b: the launch is the group, no larger than the blocks the device holds at
-// once, and its share of the device is held (GroupBudget), so all of it is resident. (Ranks
-// from a counter cost each block a claim, one after another: 255 blocks, 522k FP32 elements,
+// once, and every solve that launches one of several blocks holds its share of the device
+// (GroupBudget), so all of it is resident. (Ranks from a counter cost each block a claim, one after another: 255 blocks, 522k FP32 elements,
 // 20.2 us per step with the counter, 16.2 without.)
 template <typename TX, typename TV, int E>
 __global__ __launch_bounds__(kBlock) void mgs_kernel(MgsDev a)
@@ -162,6 +162,64 @@ hipError_t mgs_dispatch(const MgsDev &d, hipStream_t s, hipEvent_t e0, hipEvent_
     default:
         if constexpr (sizeof(TV) < 8) return mgs_go<TX, TV, 64>(d, Gi, s, e0, e1);
         return hipErrorInvalidValue;
+    }
+}
+
+// ---- step 0 without a share of the device -----------------------------------------------
+// ||r_0|| and w_1 = r_0 / ||r_0|| for a problem that joins an engine: its submission holds no
+// share of the device and must not wait for one, so no block here waits for another. The
+// first launch adds the blocks' partials in block order in its last block and sets beta (or
+// the zero-right-hand-side stop); the second scales. (Eight submissions of 512^2 x 360, FP32:
+// 257 us with the waiting group's one launch, 270 with two.)
+template <typename TX>
+__global__ __launch_bounds__(kBlock) void start_norm_kernel(MgsDev a, unsigned *count)
+{
+    __shared__ double lds[kWaves];
+    __shared__ int last;
+    const TX *q = static_cast<const TX *>(a.q);
+    constexpr int kTrip = kCombU * kBlock;
+    double ss = 0.0;
+    for (long long l0 = (long long)blockIdx.x * kTrip + threadIdx.x; l0 < a.L;
+         l0 += (long long)gridDim.x * kTrip) {
+        double v[kCombU];
+#pragma unroll
+        for (int u = 0; u < kCombU; ++u) v[u] = l0 + u * kBlock < a.L ? to_f64(q[l0 + u * kBlock]) : 0.0;
+#pragma unroll
+        for (int u = 0; u < kCombU; ++u) ss = fma(v[u], v[u], ss);
+    }
+    ss = block_sum(ss, lds);
+    if (threadIdx.x == 0) {
+        agent_store(a.partials + blockIdx.x, ss);
+        last = count_in(count, gridDim.x);
+    }
+    __syncthreads();
+    if (!last) return;
+    double t = 0.0;
+    for (int j = threadIdx.x; j < (int)gridDim.x; j += kBlock) t += agent_load(a.partials + j);
+    t = block_sum(t, lds);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double hn = sqrt(t);
+        a.hcol[0] = hn;
+        a.st->hnext = hn;
+        a.st->qnorm0 = hn;
+        if (!isfinite(hn)) a.st->error |= 2;
+    }
+    mgs_tail(a, 0);
+}
+
+template <typename TX, typename TV>
+__global__ __launch_bounds__(kBlock) void start_scale_kernel(MgsDev a)
+{
+    const double hn = a.st->hnext;
+    const bool zero = !isfinite(hn) || !(hn > a.bd_rel * hn);
+    const TX *q = static_cast<const TX *>(a.q);
+    TV *vo = static_cast<TV *>(a.vout);
+    TX *cu = static_cast<TX *>(a.cur);
+    for (long long l = (long long)blockIdx.x * kBlock + threadIdx.x; l < a.L; l += (long long)gridDim.x * kBlock) {
+        const TV w = zero ? zero_of<TV>() : from_f64<TV>(to_f64(q[l]) / hn);
+        vo[l] = w;
+        cu[l] = (TX)to_f64(w);
     }
 }
 
@@ -483,6 +541,33 @@ hipError_t launch_mgs(const MgsLaunch &m, hipStream_t s)
     if (m.tv == ABG_F32) return mgs_dispatch<float, float>(d, s, ps.e0, ps.e1);
     if (m.tv == ABG_BF16) return mgs_dispatch<float, bf16>(d, s, ps.e0, ps.e1);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_start(const MgsLaunch &m, double *partials, unsigned *count, hipStream_t s)
+{
+    MgsDev d{};
+    d.q = m.q;
+    d.L = m.L;
+    d.hcol = m.hcol;
+    d.vout = m.vout;
+    d.cur = m.cur;
+    d.partials = partials;
+    d.st = m.st;
+    d.bd_rel = m.bd_rel;
+    d.set_beta = m.set_beta;
+    if (m.k != 0 || m.step != 0 || m.giv_H) return hipErrorInvalidValue;
+    const dim3 norm(blocks_for((m.L + kCombU - 1) / kCombU, 512)), scale(blocks_for(m.L));
+    auto go = [&](auto x, auto v) {
+        using TX = decltype(x);
+        using TV = decltype(v);
+        start_norm_kernel<TX><<<norm, kBlock, 0, s>>>(d, count);
+        start_scale_kernel<TX, TV><<<scale, kBlock, 0, s>>>(d);
+        return hipGetLastError();
+    };
+    if (m.tx == ABG_F64 && m.tv == ABG_F64) return go(0.0, 0.0);
+    if (m.tx == ABG_F32 && m.tv == ABG_F32) return go(0.f, 0.f);
+    if (m.tx == ABG_F32 && m.tv == ABG_BF16) return go(0.f, bf16{});
+    return hipErrorInvalidValue;   // no engine of that precision
 }
 
 hipError_t launch_combine(int tout, const void *base, double base_coef, int tv, const void *V,

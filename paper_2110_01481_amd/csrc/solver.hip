@@ -397,8 +397,9 @@ struct Solve {
 
     // Initialisation without a host synchronisation: scratch cleared, b - A x0,
     // r0 = (B)(b - A x0), and MGS step 0 (beta = ||r0|| into dst->hnext and g[0], w_1).
-    // init: the solve's initial scalars (null: the caller owns *dst)
-    int init_async(const void *b, const void *x0, const DevState &init)
+    // init: the solve's initial scalars. held: the caller holds the share of the device that
+    // step 0's block group needs.
+    int init_async(const void *b, const void *x0, const DevState &init, bool held)
     {
         const long long m = g.m();
         // one launch: the scalars, empty reduction slots, zeroed counters, H and g, the
@@ -429,7 +430,9 @@ struct Solve {
         }
         MgsLaunch M0 = mgs_args(r0, 0);
         M0.set_beta = 1;
-        CK(launch_mgs(M0, s));
+        long long units = 0;   // 0: a group of one block, which waits for nobody
+        if (!held) CK(mgs_group_units(p.proj, p.basis, ly.L, q64 != nullptr, &units));
+        CK(units == 0 ? launch_mgs(M0, s) : launch_start(M0, part, count, s));
         return ABG_OK;
     }
 };
@@ -489,7 +492,7 @@ int instance_init(const Geometry &g, int method, int kind, int k_max, abg_stop s
 {
     Solve S(g, method, kind, k_max, st, p, s, ws);
     S.dst = dst;
-    return S.init_async(b, x0, init);
+    return S.init_async(b, x0, init, false);
 }
 
 int instance_form_x(const Geometry &g, int method, int kind, int k_max, abg_stop st,
@@ -549,7 +552,7 @@ int run_solver(const Geometry &g, int method, int kind, const void *b, const voi
 
     // b - A x0, r0 = (B)(b - A x0), beta = ||r0|| into g[0], w_1; the host learns beta
     // (and a zero right-hand side or a NaN) from the scalars of step 1
-    RC(S.init_async(b, x0, init));
+    RC(S.init_async(b, x0, init, true));
     DevState hs;
     bool zero_rhs = false;
     {

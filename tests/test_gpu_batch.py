@@ -491,3 +491,49 @@ def test_forward_items_in_tiles_per_xcd(gpu_lib, method):
         assert all(torch.equal(a.x, b.x) for a, b in zip(outs[0], o))
     for g in geoms:
         g.close()
+
+
+@pytest.mark.parametrize("proj,basis", [("f64", "f64"), ("f32", "f32"), ("f32", "bf16")])
+@pytest.mark.parametrize("N,n_ang,n_det", [(90, 90, 91), (91, 91, 92), (512, 60, 725), (1450, 20, 1451)])
+@pytest.mark.parametrize("method", ["ab", "ba"])
+def test_joining_problem_launches_no_waiting_group(gpu_lib, proj, basis, N, n_ang, n_det, method):
+    """A problem's submission holds no share of the device, so its step 0 must not be a block
+    group that waits on the device (the only launches counted as "mgs" outside a round) unless
+    the group is one block (vectors of up to 8192 elements in FP64, 16384 below). One step then
+    gives the oracle's x_1 = (<A v, r> / ||A v||^2) v, v = B r_0, r_0 = b, within the rounding of
+    the basis (FP64 1e-12, FP32 1e-5, BF16 2e-2); a zero right-hand side is still found."""
+    import torch
+    abg = gpu_lib
+    gg = abg.Geometry(N, n_ang, n_det)
+    dt = torch.float64 if proj == "f64" else torch.float32
+    b = torch.tensor(np.random.default_rng(15).uniform(size=gg.m), dtype=dt, device="cuda")
+    L = gg.m if method == "ab" else gg.n
+    eng = abg.Engine(proj=proj, basis=basis, max_slots=2)
+    abg.profile_enable(True)
+    try:
+        abg.profile_read()
+        assert eng.submit(abg.Problem(g=gg, method=method, b=b, k_max=1, stop="none", tag=0)) is not None
+        assert eng.submit(abg.Problem(g=gg, method=method, b=torch.zeros_like(b), k_max=1, stop="none", tag=1)) is not None
+        counts = abg.profile_read()
+    finally:
+        abg.profile_enable(False)
+    assert counts["mgs"][0] == (2 if L <= (8192 if basis == "f64" else 16384) else 0)
+    out = {}
+    for _ in range(20):
+        eng.step()
+        out.update((r.status, r) for _, r in eng.poll())
+        if len(out) == 2:
+            break
+    assert set(out) == {"ok", "zero_rhs"} and float(out["zero_rhs"].x.abs().max()) == 0.0
+    # both methods: x_1 = y B b, y minimising the method's own residual
+    v = gg.bp(b).double()
+    q = gg.fp(v.to(dt)).double()
+    if method == "ab":
+        y = torch.dot(q, b.double()) / torch.dot(q, q)
+    else:
+        w = gg.bp(q.to(dt)).double()
+        y = torch.dot(w, v) / torch.dot(w, w)
+    tol = {"f64": 1e-12, "f32": 1e-5, "bf16": 2e-2}[basis]
+    assert float((out["ok"].x.double() - y * v).norm() / (y * v).norm()) <= tol
+    eng.close()
+    gg.close()
