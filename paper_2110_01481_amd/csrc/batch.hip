@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kBlock) void bmgs_kernel(const BatchInst *__restric
         const BatchInst &d = D[slot];
         DevState *st = S + slot;
         const int k = st->kcur;
-        if (halted(st, k)) continue;
+        if (block_halted(st, k)) continue;
         MgsDev a;
         a.q = gfield<const TX>(d.q);
         a.V = gfield<const TV>(d.V);
@@ -508,9 +508,7 @@ __global__ __launch_bounds__(kBlock) void bmgs_kernel(const BatchInst *__restric
         if constexpr (E == 0) mgs_stream_body<TX, TV>(a, rank, d.mgs_G, lds);
         else mgs_body<TX, TV, E>(a, rank, d.mgs_G, lds, &il);
         // the Givens update by rank 0, unless this step raised an error
-        if (rank != 0) continue;
-        __syncthreads();
-        if (!halted(st, k)) mgs_tail(a, rank);
+        if (rank == 0 && !block_halted(st, k)) mgs_tail(a, rank);
     }
 }
 

@@ -607,6 +607,12 @@ __device__ inline void givens_wave_n(double *H, int ld, double *R, double *cs, d
     }
 }
 
+// halted(), one answer for the whole block (every thread calls it). Another rank of a group
+// can raise the error flag while this block reads it (a bounded wait that is used up): a block
+// that takes several items must not have some waves leave for the next one and others not,
+// as both paths hold barriers.
+__device__ inline bool block_halted(const DevState *st, int k) { return __syncthreads_or(halted(st, k)) != 0; }
+
 // After the normalisation, by the block of rank 0: step 0 sets beta = ||r_0|| and
 // activates the solve (or raises the zero-right-hand-side stop), step k >= 1 runs the
 // Givens update of column k, then copies the scalars to the host slot.
