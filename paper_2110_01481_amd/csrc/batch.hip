@@ -688,6 +688,14 @@ struct Engine {
     hipGraph_t graph[2] = {};
     hipGraphExec_t exec[2] = {};
     bool dirty = true;
+    // graphs given up while their rounds may still be running, freed once round `last` has run
+    struct Retired {
+        hipGraph_t graph;
+        hipGraphExec_t exec;
+        long long last;
+    };
+    std::vector<Retired> retired;
+    long long ring_round[kSnapRing] = {};   // rounds enqueued before each snapshot
     unsigned need = 0;   // lists (bit t: list t) that a submitted problem has needed
     Tiles tiles{0, 64, 2};
     int grid_proj = 0, grid_back = 0, grid_back64 = 0, grid_back_adj = 0, grid_back64_adj = 0;
@@ -713,10 +721,8 @@ struct Engine {
             (void)hipStreamSynchronize(cb_stream);
             (void)hipStreamDestroy(cb_stream);
         }
-        for (int v = 0; v < 2; ++v) {
-            if (exec[v]) (void)hipGraphExecDestroy(exec[v]);
-            if (graph[v]) (void)hipGraphDestroy(graph[v]);
-        }
+        retire();
+        (void)free_retired(rounds);
         for (auto &e : ev)
             if (e) (void)hipEventDestroy(e);
         for (auto &e : tev)
@@ -864,20 +870,39 @@ struct Engine {
         return most < kForkMaxBytes;
     }
 
-    // Drops both captured variants once the tiles changed; captures variant v if absent.
+    // Gives up both captured variants; rounds of them may still be running.
+    void retire()
+    {
+        for (int u = 0; u < 2; ++u) {
+            if (graph[u]) retired.push_back({graph[u], exec[u], rounds});
+            exec[u] = nullptr;
+            graph[u] = nullptr;
+        }
+    }
+    // Frees the graphs whose rounds are among the first `done`.
+    hipError_t free_retired(long long done)
+    {
+        hipError_t first = hipSuccess;
+        size_t kept = 0;
+        for (const Retired &r : retired) {
+            if (r.last > done) {
+                retired[kept++] = r;
+                continue;
+            }
+            const hipError_t e = r.exec ? hipGraphExecDestroy(r.exec) : hipSuccess;
+            const hipError_t g = hipGraphDestroy(r.graph);
+            if (first == hipSuccess) first = e != hipSuccess ? e : g;
+        }
+        retired.resize(kept);
+        return first;
+    }
+
+    // Gives up both captured variants once the tiles or the lists changed; captures variant
+    // v if absent. The rounds in flight go on meanwhile.
     int capture(int v)
     {
-        if (dirty) {
-            // a round of the old graph may still be running
-            if (exec[0] || exec[1]) BCK(hipStreamSynchronize(s));
-            for (int u = 0; u < 2; ++u) {
-                if (exec[u]) BCK(hipGraphExecDestroy(exec[u]));
-                if (graph[u]) BCK(hipGraphDestroy(graph[u]));
-                exec[u] = nullptr;
-                graph[u] = nullptr;
-            }
-            dirty = false;
-        }
+        if (dirty) retire();
+        dirty = false;
         if (exec[v]) return ABG_OK;
         BCK(hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal));
         enqueue_round(cap_stream, v ? cap_stream2 : nullptr);
@@ -1190,6 +1215,7 @@ struct Engine {
         const int r = inflight.front();
         inflight.pop_front();
         BCK(hipEventSynchronize(ev[r]));
+        if (!retired.empty()) BCK(free_retired(ring_round[r]));
         return process(h_snap + (size_t)r * max_slots);
     }
 
@@ -1223,6 +1249,7 @@ struct Engine {
         }
         const int r = ring_next;
         ring_next = (ring_next + 1) % kSnapRing;
+        ring_round[r] = rounds;
         static_assert(sizeof(DevState) % 8 == 0, "copied in words of eight bytes");
         const int words = (int)(sizeof(DevState) / 8) * max_slots;
         snap_kernel<<<(words + 255) / 256, 256, 0, s>>>(

@@ -537,3 +537,45 @@ def test_joining_problem_launches_no_waiting_group(gpu_lib, proj, basis, N, n_an
     assert float((out["ok"].x.double() - y * v).norm() / (y * v).norm()) <= tol
     eng.close()
     gg.close()
+
+
+def test_first_problem_of_a_kind_joins_without_a_wait(gpu_lib):
+    """The captured round changes when a problem first needs a kernel that none before it did.
+    The rounds in flight go on meanwhile: with about 0.3 s of work queued on the engine's
+    stream, the step that takes the new round returns while that work still runs. Every result
+    is what the problem gives alone, bit for bit."""
+    import torch
+    abg = gpu_lib
+    big, gg = abg.Geometry(2048, 1800, 2897), abg.Geometry(128, 60, 183)
+    rng = np.random.default_rng(16)
+    kinds = [("ab", "hat", "none"), ("ba", "hat", "none"), ("ab", "adj", "none"), ("ba", "adj", "dp")]
+    bs = [torch.tensor(rng.uniform(size=gg.m), dtype=torch.float32, device="cuda") for _ in kinds]
+    probs = [abg.Problem(g=gg, method=m, b=b, k_max=20, stop=st, tau=1.0, noise_norm=1e-6, bp=bp, tag=i)
+             for i, ((m, bp, st), b) in enumerate(zip(kinds, bs))]
+    x = torch.rand(big.n, dtype=torch.float64, device="cuda")
+    y = torch.empty(big.m, dtype=torch.float64, device="cuda")
+    big.fp(x, out=y)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    eng = abg.Engine(proj="f32", basis="f32", max_slots=4, stream=s)
+    tags = [eng.submit(probs[0])]
+    out = {}
+    for p in probs[1:]:
+        s.synchronize()
+        eng.step()
+        out.update(eng.poll())
+        s.synchronize()
+        for _ in range(150):
+            big.fp(x, out=y, stream=s)
+        tags.append(eng.submit(p))
+        eng.step()
+        assert not s.query()
+    while len(out) < len(probs):
+        eng.step()
+        out.update(eng.poll())
+    eng.close()
+    for t, p in zip(tags, probs):
+        alone = abg.Engine(proj="f32", basis="f32", max_slots=1).run([p])[0]
+        assert torch.equal(alone.x, out[t].x) and alone.k_done == out[t].k_done
+    big.close()
+    gg.close()
