@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/abgmres.h"
+#include "launch_plan.h"
 #include "geometry.h"
 #include "group_budget.h"
 
@@ -213,14 +214,7 @@ void ncp_force_goertzel(int on);
 // Process-wide: forward projector block shape, 2^lg_apb angles per block (0..2), or -1 for
 // the automatic choice (tests and measurements).
 void fwd_force_block_shape(int lg_apb);
-// How a geometry's forward projection is launched (the choice single solves make, with
-// the forced settings applied).
-struct FwdPlan {
-    int nw;      // line and Joseph models: waves (angles) per block of the staged kernel; 0: direct
-    int share;   // eighths of the staged kernel's blocks that stage (8: all)
-    bool tiled;  // staged kernel: blocks dealt out in tiles, one XCD each
-    int lg;      // direct kernel: log2 of the angles per block of 256 threads
-};
+// The launch of a geometry's forward projection (launch_plan.h), with the forced settings.
 FwdPlan fwd_plan(const Geometry &g, int dtype);
 // Eighths of staged blocks that stage: the forced share, or all.
 int fwd_stage_share();

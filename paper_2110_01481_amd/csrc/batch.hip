@@ -49,10 +49,12 @@ enum Tab {
     kTBackAB,      // t = B w_k (AB), interpolating back projector
     kTBackABAdj,   // t = A^T w_k (AB), matched pair
     kTFwdBA,       // z = A w_k (BA)
+    kTFwdBATwo,    // the same, problems whose items walk two bands per trip (FwdPlan::two)
     kTPadAB,       // pad t (AB)
     kTBackBA,      // q = B z (BA), interpolating back projector
     kTBackBAAdj,   // q = A^T z (BA), matched pair
     kTFwdAB,       // q = A t (AB)
+    kTFwdABTwo,    // the same, two bands per trip
     kTMgsS,        // MGS groups with the small register tile
     kTMgsL,        // MGS groups with the large register tile
     kTMgsH,        // MGS groups with the largest register tile (FP32/BF16 basis)
@@ -87,6 +89,7 @@ struct BatchInst {
     int mgs_G, mgs_class;   // register tile class 0 small, 1 large, 3 huge; 2 streaming
     int chunk, n_chunks;
     int fwd_rays;           // forward block shape of the single-solve rule (tiles.rays = 0)
+    int fwd_two;            // FwdPlan::two
     FwdOrder fwd_order;     // four-angle forward items in tiles per XCD (rows > 0: large images)
 };
 
@@ -150,8 +153,12 @@ __device__ int items_of(int t, const BatchInst &d, const Tiles &tl)
         return ceil_div(d.N, kTile) * ceil_div(d.N, kTile);
     }
     case kTFwdBA:
-    case kTFwdAB: {
-        if ((t == kTFwdBA) != ba) return 0;
+    case kTFwdBATwo:
+    case kTFwdAB:
+    case kTFwdABTwo: {
+        const bool want_ba = t == kTFwdBA || t == kTFwdBATwo;
+        const bool want_two = t == kTFwdBATwo || t == kTFwdABTwo;
+        if (ba != want_ba || (d.fwd_two != 0) != want_two) return 0;
         const int rays = tl.rays ? tl.rays : d.fwd_rays;
         // whole eights, so that item i of a problem runs on XCD i mod 8 (fwd_item)
         if (in_tiles(d, tl, rays)) return (int)d.fwd_order.blocks();
@@ -395,8 +402,10 @@ __global__ __launch_bounds__(256) void bpad_kernel(const BatchInst *__restrict__
     });
 }
 
-// mode 0: BA, z = A w_k (column k of Z);  mode 1: AB, q = A t
-template <typename T>
+// mode 0: BA, z = A w_k (column k of Z);  mode 1: AB, q = A t. TRIP: bands per trip of the
+// items that do not stage. One kernel per trip (their lists are separate), as both walks in
+// one kernel spill.
+template <typename T, int TRIP>
 __global__ __launch_bounds__(256, 8) void bfwd_kernel(const BatchInst *__restrict__ D, const DevState *S,
                                                    TabView tv, int t, int mode, Tiles tl)
 {
@@ -418,16 +427,16 @@ __global__ __launch_bounds__(256, 8) void bfwd_kernel(const BatchInst *__restric
         if (rays == 64 && tl.stage > 0 &&
             (int)(((unsigned)local * 0x9E3779B1u + (unsigned)slot * 0x85EBCA6Bu) >> 29) < tl.stage) {
             T *y = mode == 0 ? zcol<T>(d, k) : gfield<T>(d.q);
-            forward_block_staged<T, 4>(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
-                                       gfield<const AngleParams>(d.ang), gy * 4, gx * 64, d.N, d.S, d.n_ang, d.n_det, d.ds, d.s0,
-                                       lds);
+            forward_block_staged<T, 4, ABG_FP_LINE, TRIP>(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
+                                       gfield<const AngleParams>(d.ang), gy * 4, gx * 64, d.N, d.S, d.n_ang, d.n_det,
+                                       d.ds, d.s0, lds);
             return;
         }
         const int a = gy * apb + wave / wpa;
         const int i = gx * rays + (wave % wpa) * 64 + lane;
         if (a >= d.n_ang) return;   // whole waves
         T *y = mode == 0 ? zcol<T>(d, k) : gfield<T>(d.q);
-        forward_ray(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
+        forward_ray<T, ABG_FP_LINE, TRIP>(gfield<const T>(d.xr), gfield<const T>(d.xc), y,
                     gfield<const AngleParams>(d.ang), a, i, d.N, d.S, d.n_det, d.ds, d.s0);
     });
 }
@@ -740,7 +749,7 @@ struct Engine {
     template <typename TX, typename TV> hipError_t capacities()
     {
         hipError_t e;
-        if ((e = capacity_of(bfwd_kernel<TX>, 256, &grid_proj)) != hipSuccess) return e;
+        if ((e = capacity_of(bfwd_kernel<TX, kChunk>, 256, &grid_proj)) != hipSuccess) return e;
         if ((e = capacity_of(bback_kernel<TX, 128, false>, kBackThreads, &grid_back)) != hipSuccess)
             return e;
         if ((e = capacity_of(bback_kernel<TX, 64, false>, kBackThreads, &grid_back64)) != hipSuccess)
@@ -794,6 +803,13 @@ struct Engine {
         }
     }
 
+    // list t (eight bands per trip) and list t + 1 (two)
+    template <typename TX> void enqueue_fwd(hipStream_t q, const Tiles &tf, int t, int mode)
+    {
+        if (needs(t)) bfwd_kernel<TX, kChunk><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, t, mode, tf);
+        if (needs(t + 1)) bfwd_kernel<TX, 2><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, t + 1, mode, tf);
+    }
+
     // begin + the three projector phases (idempotent between rounds: they recompute the
     // round's z, t and q from w_k without advancing any problem). The BA chain (pad,
     // forward, back) and the AB chain (back, pad, forward) touch disjoint problems and
@@ -807,7 +823,7 @@ struct Engine {
         begin_kernel<<<kNumTab, 256, 0, q>>>(d_desc, d_st, tv, max_slots, tl);
         Tiles tf = tl;
         tf.stage = fwd_stage_share();
-        const bool ba = needs(kTFwdBA), ab = needs(kTFwdAB);
+        const bool ba = needs(kTPadBA), ab = needs(kTPadAB);
         const bool fork = q2 && ba && ab;
         const hipStream_t qa = fork ? q2 : q;
         if (fork) {
@@ -816,10 +832,10 @@ struct Engine {
         }
         if (ba) bpad_kernel<TX><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, kTPadBA, 0, tl);
         if (ab) enqueue_back<TX>(qa, tl, kTBackAB, 0);
-        if (ba) bfwd_kernel<TX><<<grid_proj, 256, 0, q>>>(d_desc, d_st, tv, kTFwdBA, 0, tf);
+        if (ba) enqueue_fwd<TX>(q, tf, kTFwdBA, 0);
         if (ab) bpad_kernel<TX><<<grid_proj, 256, 0, qa>>>(d_desc, d_st, tv, kTPadAB, 1, tl);
         if (ba) enqueue_back<TX>(q, tl, kTBackBA, 1);
-        if (ab) bfwd_kernel<TX><<<grid_proj, 256, 0, qa>>>(d_desc, d_st, tv, kTFwdAB, 1, tf);
+        if (ab) enqueue_fwd<TX>(qa, tf, kTFwdAB, 1);
         if (fork) {
             (void)hipEventRecord(join_ev, q2);
             (void)hipStreamWaitEvent(q, join_ev, 0);
@@ -983,6 +999,7 @@ struct Engine {
         d.need_res = r.stop.kind == ABG_STOP_DP;
         const FwdPlan fp = fwd_plan(g, p.proj);
         d.fwd_rays = fp.nw > 0 ? 64 : 256 >> fp.lg;
+        d.fwd_two = fp.two;
         d.fwd_order = FwdOrder::make((g.n_det + 63) / 64, (g.n_ang + 3) / 4, fp.tiled);
         // Gram-Schmidt class: the smallest register tile whose block group the device
         // holds at once (the small tile while its group stays small), else the streaming
@@ -1038,8 +1055,8 @@ struct Engine {
         unsigned lists = need | 1u << (d.mgs_class == 0 ? kTMgsS : d.mgs_class == 1 ? kTMgsL
                                                                : d.mgs_class == 3 ? kTMgsH : kTMgsX);
         const bool ba = r.method == ABG_METHOD_BA, adj = r.bp_kind == ABG_BP_ADJ;
-        lists |= ba ? 1u << kTPadBA | 1u << kTFwdBA | 1u << (adj ? kTBackBAAdj : kTBackBA)
-                    : 1u << kTPadAB | 1u << kTFwdAB | 1u << (adj ? kTBackABAdj : kTBackAB);
+        lists |= ba ? 1u << kTPadBA | 1u << (fp.two ? kTFwdBATwo : kTFwdBA) | 1u << (adj ? kTBackBAAdj : kTBackBA)
+                    : 1u << kTPadAB | 1u << (fp.two ? kTFwdABTwo : kTFwdAB) | 1u << (adj ? kTBackABAdj : kTBackAB);
         if (d.need_res) lists |= 1u << kTRes;
         if (lists != need) {
             need = lists;

@@ -218,6 +218,9 @@ int abg_create_geometry(int N, int n_ang, double ang_start_deg, double ang_range
         g.theta[a] = th;
         g.host[a] = make_angle(th, det_spacing);
     }
+    for (int f32 = 0; f32 < 2; ++f32)
+        g.fit[f32] = {stage_fit(g.host, N, det_spacing, 4, stage_cols(f32 ? 4 : 8)),
+                      stage_fit(g.host, N, det_spacing, 8, stage_cols(f32 ? 4 : 8))};
     if (hipGetDevice(&g.device) != hipSuccess ||
         hipMalloc((void **)&g.dev, sizeof(AngleParams) * n_ang) != hipSuccess) {
         delete h;

@@ -289,13 +289,12 @@ __device__ inline void load_quad_row(const T *row, int S, int col, Taps<T> (&t)[
 // Ray i of angle a (i may exceed n_det: such lanes only take part in the wave's band
 // range and store nothing). Called by whole waves of consecutive rays.
 //
-// A group of bands per trip, their loads issued before their use: this walk serves
-// launches of few waves and, among staged blocks, those whose angles lie far apart, which
-// both wait on the gather latency (512^2 x 60 angles: 87 us with two bands per trip, 40 with
-// eight; a launch that fills the device many times over is better off with two, 3.2 against
-// 3.9 ms at 2048^2 x 1800 in FP64, but it stages its rows).
-// bands' weights and positions: BandWeights.
-template <typename T, int MODEL = ABG_FP_LINE>
+// TRIP bands per trip, their loads issued before their use. Launches of few waves, and few
+// blocks that cannot stage among many that do, wait on the gather latency (512^2 x 60 angles:
+// 87 us with two bands per trip, 40 with eight). Where a full device walks so, two keep more of
+// the rows that neighbouring waves read in the caches (plan_forward); the loop over trips stays
+// rolled, or the compiler moves their loads together again.
+template <typename T, int MODEL = ABG_FP_LINE, int TRIP = kChunk>
 __device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict__ xc,
                                    T *__restrict__ y, const AngleParams *__restrict__ ang, int a,
                                    int i, int N, int S, int n_det, double ds, double s0)
@@ -391,25 +390,29 @@ __device__ inline void forward_ray(const T *__restrict__ xr, const T *__restrict
                     if (kTrip < kChunk) asm volatile("" ::: "memory");
                 }
             } else {
-                int c[kChunk];
-                T w[kChunk], v0[kChunk], v1[kChunk];
+#pragma unroll 1
+                for (int j0 = 0; j0 < kChunk; j0 += TRIP) {
+                    int c[TRIP];
+                    T w[TRIP], v0[TRIP], v1[TRIP];
 #pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    c[j] = band.column_raw();
-                    w[j] = band.left_share(bw);
-                    band.next();
-                }
-                // bands past the image read as zero
+                    for (int j = 0; j < TRIP; ++j) {
+                        c[j] = band.column_raw();
+                        w[j] = band.left_share(bw);
+                        band.next();
+                    }
+                    // bands past the image read as zero
 #pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    const Taps<T> t = load_taps_row(row + (size_t)j * S, r + j < N ? S : 0, c[j]);
-                    v0[j] = t.a;
-                    v1[j] = t.b;
-                }
+                    for (int j = 0; j < TRIP; ++j) {
+                        const int b = j0 + j;
+                        const Taps<T> t = load_taps_row(row + (size_t)b * S, r + b < N ? S : 0, c[j]);
+                        v0[j] = t.a;
+                        v1[j] = t.b;
+                    }
 #pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    sum.tap(w[j], v0[j]);
-                    sum.tap(T(1) - w[j], v1[j]);
+                    for (int j = 0; j < TRIP; ++j) {
+                        sum.tap(w[j], v0[j]);
+                        sum.tap(T(1) - w[j], v1[j]);
+                    }
                 }
             }
             sum.group_done();
@@ -474,7 +477,7 @@ struct FwdOrder {
 // which used to bound it at one scalar instruction per cycle and CU). Blocks whose angles
 // differ in orientation, include an axis-aligned or a missing angle, or need a wider
 // window take the walk above.
-template <typename T> constexpr int kStageCols = 64 * 16 / (int)sizeof(T);
+template <typename T> constexpr int kStageCols = stage_cols(sizeof(T));
 
 template <typename T, int NW> struct FwdStageLds {
     T win[2][kChunk][kStageCols<T>];
@@ -499,7 +502,7 @@ __device__ inline long long uniform_ll(long long v)
 // Angles a0 .. a0 + 3 (wave w takes a0 + w), rays ray0 .. ray0 + 63 of each. All four
 // waves call it (also for angles past n_ang); it starts with a block-wide barrier, so
 // that consecutive calls of a block may share L.
-template <typename T, int NW, int MODEL = ABG_FP_LINE>
+template <typename T, int NW, int MODEL = ABG_FP_LINE, int TRIP = kChunk>
 __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *__restrict__ xc,
                                             T *__restrict__ y, const AngleParams *__restrict__ ang,
                                             int a0, int ray0, int N, int S, int n_ang, int n_det,
@@ -571,7 +574,7 @@ __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *_
         staged = fmax(hb - lb, he - le) + (kChunk - 1) * fabs(slope) + 6.0 <= (double)W;
     }
     if (!staged) {
-        if (a < n_ang) forward_ray<T, MODEL>(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
+        if (a < n_ang) forward_ray<T, MODEL, TRIP>(xr, xc, y, ang, a, i, N, S, n_det, ds, s0);
         return;
     }
     T acc = T(0);

@@ -28,6 +28,12 @@ struct AngleParams {
     int axis;           // 1 when q == 0 (ray parallel to a pixel edge)
 };
 
+// Shares of the groups of four and of eight listed angles that the staged forward walk can
+// take (stage_fit).
+struct StageFit {
+    double four = 0.0, eight = 0.0;
+};
+
 struct Geometry {
     int N = 0, n_ang = 0, n_det = 0;
     double ds = 1.0;
@@ -38,6 +44,7 @@ struct Geometry {
     int device = 0;
     std::vector<double> theta;
     std::vector<AngleParams> host;
+    StageFit fit[2];          // FP64, FP32
     AngleParams *dev = nullptr;
     // NCP periodogram tables (chirp transform of the row length), built on first use
     mutable void *ncp_tab = nullptr;

@@ -64,7 +64,7 @@ struct FwdShape {
 // (FP64), gathers 1.1e8 -> 1.6e7 per launch. A share
 // of the blocks below eight eighths (tests and measurements; spread over the grid by a hash
 // of the block) stages, the others take their taps straight from the image copies.
-template <typename T, int NW, int MODEL>
+template <typename T, int NW, int MODEL, int TRIP>
 __global__ __launch_bounds__(64 * NW) void forward_staged_kernel(
     const T *__restrict__ xr, const T *__restrict__ xc, T *__restrict__ y,
     const AngleParams *__restrict__ ang, int N, int S, int n_ang, int n_det, double ds,
@@ -76,14 +76,14 @@ __global__ __launch_bounds__(64 * NW) void forward_staged_kernel(
     if (!ord.block(blockIdx.x, gx, gy)) return;
     const unsigned b = (unsigned)(gy * ord.ngx + gx);
     if ((int)((b * 0x9E3779B1u) >> 29) < stage_eighths) {
-        forward_block_staged<T, NW, MODEL>(xr, xc, y, ang, gy * NW, gx * 64, N, S, n_ang, n_det, ds,
+        forward_block_staged<T, NW, MODEL, TRIP>(xr, xc, y, ang, gy * NW, gx * 64, N, S, n_ang, n_det, ds,
                                            s0, lds);
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int a = gy * NW + wave;
     if (a >= n_ang) return;
-    forward_ray<T, MODEL>(xr, xc, y, ang, a, gx * 64 + ((int)threadIdx.x & 63), N, S, n_det, ds, s0);
+    forward_ray<T, MODEL, TRIP>(xr, xc, y, ang, a, gx * 64 + ((int)threadIdx.x & 63), N, S, n_det, ds, s0);
 }
 
 // Every ray by itself, MODEL = ABG_FP_LINE, ABG_FP_STRIP or ABG_FP_JOSEPH.
@@ -190,7 +190,9 @@ hipError_t forward_t(const Geometry &g, const void *x, void *y, void *ws, hipStr
         const size_t blocks = ord.blocks();
         auto pick = [&](auto model) {
             constexpr int M = decltype(model)::value;
-            return plan.nw == 8 ? forward_staged_kernel<T, 8, M> : forward_staged_kernel<T, 4, M>;
+            return plan.nw == 8 ? forward_staged_kernel<T, 8, M, kChunk>
+                   : plan.two   ? forward_staged_kernel<T, 4, M, 2>
+                                : forward_staged_kernel<T, 4, M, kChunk>;
         };
         auto fn = g.model == ABG_FP_LINE ? pick(std::integral_constant<int, ABG_FP_LINE>{})
                                          : pick(std::integral_constant<int, ABG_FP_JOSEPH>{});
@@ -270,43 +272,9 @@ int fwd_stage_share()
     return share >= 0 ? share : 8;
 }
 
-// From measurements on gfx950 (every choice gives the same bits; us per apply, FP64 /
-// FP32; waves = 64-ray groups times angles, fan = N times the angle step in radians, the
-// pixels by which the rays of adjacent angles drift apart across the image):
-//  - Staged in LDS from 2048 waves on (512^2 x 180 angles, 2160 waves: direct 51 / 49, staged
-//    48 / 43; 1024^2 x 180: 156 / 154 and 105 / 92; 512^2 x 720: 107 / 104 and 89 / 73; below,
-//    256^2 x 180, 1080 waves: 22 / 22 and 23 / 22). Blocks whose angles lie too far apart
-//    for one window take the direct walk by themselves.
-//  - Eight angles per block, which halves the copies into LDS of four, once the device holds
-//    two rounds of them (16384 waves) and their windows fit: eight rays drift apart by up to
-//    0.7 x 7 fan, and the window of 128 (FP64) or 256 (FP32) columns spends 102 on the 64 rays
-//    and its margins (fan <= 5 / 30; 2048^2 x 1800: 2300 / 1680 with four, 2050 / 1570 with
-//    eight; 2048^2 x 600, fan 10.7: 940 / 648 and 981 / 604; 1536^2 x 360, 12240 waves: 307 / 254
-//    and 401 / 275).
-//  - Tiles per XCD above N = 896, where the image no longer stays in a 4 MB L2 by itself
-//    (2048^2 x 1800: 2256 / 1760 without, 2100 / 1580 with tiles; 1024^2 x 720: 322 / 265 and
-//    300 / 247; 640^2 x 720, 141 / 110 and 151 / 124, is better without).
-//  - Direct launches (and the other models): one angle per block, or two where that leaves
-//    fewer lanes of the last block idle, up to N = 512; four above.
-// A grid of 2^31 lanes or more stays with the direct kernel, whose grid has two dimensions.
 FwdPlan fwd_plan(const Geometry &g, int dtype)
 {
-    const int forced = g_fwd_force_lg.load(std::memory_order_relaxed);
-    const long long groups = (g.n_det + 63LL) / 64, waves = groups * g.n_ang;
-    FwdPlan p{};
-    p.share = fwd_stage_share();
-    p.tiled = g.N > 896;
-    const long long lanes1 = (g.n_det + 255LL) / 256 * 256, lanes2 = (g.n_det + 127LL) / 128 * 128;
-    p.lg = forced >= 0 ? forced : g.N > 512 ? 2 : lanes2 < lanes1 ? 1 : 0;
-    // mean step between listed angles
-    const double step = g.n_ang > 1 ? std::fabs(g.theta.back() - g.theta.front()) / (g.n_ang - 1) *
-                                          (3.14159265358979323846 / 180.0)
-                                    : 1.0;
-    const bool wide = waves >= 16384 && g.N * step <= (dtype == ABG_F64 ? 5.0 : 30.0);
-    if (forced == 2) p.nw = 4;
-    else if (forced < 0 && waves >= 2048) p.nw = wide ? 8 : 4;
-    if (p.share == 0 || waves >= (1LL << 31) / 64) p.nw = 0;
-    return p;
+    return plan_forward(g, dtype_size(dtype), g_fwd_force_lg.load(std::memory_order_relaxed), fwd_stage_share());
 }
 
 void fwd_force_block_shape(int lg_apb) { g_fwd_force_lg.store(lg_apb >= 0 && lg_apb <= 2 ? lg_apb : -1); }

@@ -155,6 +155,49 @@ def test_forward_staged_launches_bit_identical(gpu_lib, kw, dt, model):
         gg.close()
 
 
+# Launches from 8192 waves on whose blocks cannot stage: those walk two bands per trip.
+FAR_GEOMS = [
+    dict(N=897, n_ang=413, n_det=1275, order="shuffled"),     # 8260 waves, ragged ends
+    dict(N=1000, n_ang=401, n_det=1409, order="interleaved"), # some blocks stage in FP64
+    dict(N=901, n_ang=1641, n_det=319, det_spacing=4.0),      # 8205 waves of bins of four pixels
+]
+
+
+@pytest.mark.parametrize("kw", FAR_GEOMS, ids=_ids)
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("model", ["line", "joseph"])
+def test_forward_far_angles_bit_identical(gpu_lib, kw, dt, model):
+    """Two bands per trip add a ray's taps in the order of eight: the bits of the direct kernel,
+    from single launches and (line model) from the engine's items."""
+    import torch
+    import paper_2110_01481_amd as abg
+    kw = dict(kw)
+    order = kw.pop("order", None)
+    if order:
+        n = kw["n_ang"]
+        a = np.arange(n) * 180.0 / n
+        kw["angles_deg"] = np.random.default_rng(9).permutation(a) if order == "shuffled" else np.concatenate([a[i::8] for i in range(8)])
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    rng = np.random.default_rng(6)
+    x = torch.tensor(rng.standard_normal(kw["N"] ** 2), dtype=tdt, device="cuda")
+    gg = abg.Geometry(**kw, model=model)
+    b = torch.tensor(rng.uniform(size=gg.m), dtype=tdt, device="cuda")
+    y = torch.full((gg.m,), float("nan"), dtype=tdt, device="cuda")
+    def in_engine():
+        p = abg.Problem(g=gg, method="ba", b=b, k_max=2, stop="none")
+        return abg.Engine(proj=dt, basis=dt, max_slots=1).run([p])[0].x
+    try:
+        gg.fp(x, out=y)
+        r = in_engine() if model == "line" else None
+        abg.fp_force_block_shape(0)
+        assert torch.equal(gg.fp(x), y)
+        if r is not None:
+            assert torch.equal(in_engine(), r)
+    finally:
+        abg.fp_force_block_shape(-1)
+        gg.close()
+
+
 # Back projections over orbits of four pixels: 16 waves (up to 256 blocks) and 8, even and odd
 # images with ragged tiles, angle counts around the 32 of a round, detectors shorter than the
 # image diagonal, both ends of the bin spacings.
