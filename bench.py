@@ -34,9 +34,10 @@ _CSRC = "paper_2110_01481_amd/csrc/"
 # kernels whose stored counter summaries (profiles/<kernel>_<workload>_counters.md) bench.py
 # reads: the kernel-name prefixes in rocprofv3's CSV (the launches a projection may take)
 # and the sources whose change makes the stored readings stale
-_FWD_SRC = [_CSRC + "fwd_body.h", _CSRC + "footprint.h", _CSRC + "geometry.h", _CSRC + "projectors.hip"]
+_FWD_SRC = [_CSRC + "fwd_body.h", _CSRC + "footprint.h", _CSRC + "geometry.h", _CSRC + "launch_plan.h",
+            _CSRC + "projectors.hip"]
 _BACK_SRC = [_CSRC + "back_body.h", _CSRC + "back_orbit.h", _CSRC + "footprint.h", _CSRC + "geometry.h",
-             _CSRC + "projectors.hip"]
+             _CSRC + "launch_plan.h", _CSRC + "projectors.hip"]
 COUNTER_KERNELS = {
     "forward_kernel_f32": (("forward_staged_kernel<float", "forward_kernel<float"), _FWD_SRC),
     "forward_kernel_f64": (("forward_staged_kernel<double", "forward_kernel<double"), _FWD_SRC),

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <vector>
 
+#include "../../include/abgmres.h"
 #include "geometry.h"
 
 namespace abg {
@@ -95,6 +96,39 @@ inline FwdPlan plan_forward(const Geometry &g, size_t elem, int forced_lg, int s
     if (share == 0 || waves >= (1LL << 31) / 64) p.nw = 0;
     p.two = p.nw == 4 && p.tiled && waves >= 8192 && fit.four < 0.5;
     return p;
+}
+
+// Waves per block of the back projectors over orbits of four pixels (back_orbit.h), or 0 for the
+// tiles of back_body.h. An orbit block covers four tiles of 16 x 16 pixels, so a CU whose share of
+// the image is ragged does up to four times the tiles' work for it; `even` says how little, in
+// percent: the tiles over four times 256 CUs times the orbit blocks of the busiest CU. Up to 64
+// angles the tiles fill one window each and the orbits' setting up counts for more. The orbits
+// are taken where they are faster (us per apply, tiles / orbits; N^2 x angles, even):
+//  - interpolating, FP32: 672 x 60, 86, 8.6 / 9.0; 817 x 60, 88, 12.4 / 12.0; 609 x 180, 74,
+//    17.6 / 19.5; 897 x 180, 79, 32.4 / 34.5; 641 x 180, 82, 19.9 / 19.6; 512 x 720, 100, 43 / 38;
+//    1024 x 720, 100, 147 / 123. FP64: 609 x 60, 74, 11.2 / 11.7, x 360 48.0 / 47.4; 433 x 60, 76,
+//    7.9 / 8.5, x 360 34.1 / 28.0; 1025 x 60, 82, 26.2 / 25.2.
+//  - matched, FP32: 817 x 33, 88, 13.0 / 13.9; 1169 x 33, 89, 23.3 / 23.5; 641 x 60, 82, 11.8 /
+//    11.5; 1025 x 60, 82, 24.5 / 25.1; 929 x 60, 84, 20.8 / 20.5; 609 x 120, 74, 18.5 / 18.7;
+//    897 x 180, 79, 49.7 / 48.2; 1249 x 180, 87, 90.6 / 80.7. FP64: 609 x 60, 74, 18.4 / 17.7; 881 x
+//    360, 76, 186 / 149.
+//  - Joseph^T, FP64, one block per CU: 417 x 60, 71, 13.3 / 13.9; 448 x 60, 76, 15.9 / 13.4; 384 x
+//    120, 56, 21.9 / 22.2, x 360 60.4 / 57.2; more: 720 x 360, 65, 154 / 165; 577 x 360, 66,
+//    116 / 108. FP32: 384 x 360, 56, 40.9 / 33.2; 720 x 33, 65, 15.4 / 13.9.
+//  - the strip kinds' tiles take two to four times as long.
+// One block per CU or less takes 16 waves (512^2 FP64 58 with 8, 51 with 16), more blocks 8.
+inline int orbit_waves(int N, int n_ang, int kind, size_t elem)
+{
+    constexpr long long kCus = 256;
+    const long long t = ((N + 1) / 2 + 15) / 16, b = t * t, per_cu = (b + kCus - 1) / kCus;
+    const long long tiles = (N + 15) / 16, even = 100 * tiles * tiles / (4 * kCus * per_cu);
+    const bool few = n_ang <= 64, f64 = elem == 8;
+    long long least = 50;
+    if (kind == ABG_BP_HAT) least = f64 ? (few ? 80 : 74) : few ? 87 : 80;
+    else if (kind == ABG_BP_ADJ) least = f64 ? 74 : n_ang <= 40 ? 89 : few ? 84 : 75;
+    else if (kind == ABG_BP_JOSEPH_T && f64) least = per_cu > 1 ? 66 : few ? 75 : 50;
+    if (even < least) return 0;
+    return per_cu == 1 ? 16 : 8;
 }
 
 }  // namespace abg

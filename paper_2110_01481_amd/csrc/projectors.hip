@@ -152,20 +152,11 @@ __global__ __launch_bounds__(64 * NWV, 4) void back_orbit_kernel(
                                                             x + (size_t)N * S, S, tau_thr);
 }
 
-// Waves per block of the orbit kernels, or 0 for the tile kernels. An orbit block covers 1024
-// pixels, so a small image leaves CUs without one: the orbits are taken where the blocks
-// spread over the 256 CUs evenly enough for what they save (us per apply, tiles / orbits,
-// interpolating kind in FP32 at 720 angles: 384^2, 56% even, 29 / 32; 512^2, 100%, 43 / 38;
-// 640^2, 78%, 68 / 65; 768^2 x 360, 75%, 44 / 48; 1024^2, 100%, 147 / 123; the three-tap kinds
-// save more: Joseph^T 384^2 66 / 54). One block per CU or less takes 16 waves (512^2 FP64 58 with
-// 8, 51 with 16), more blocks 8. Sinograms of 2 GiB or more take the tiles' 64-bit addresses.
+// Waves per block of the orbit kernels, or 0 for the tile kernels. Sinograms of 2 GiB or more
+// take the tiles' 64-bit addresses.
 int back_orbit_waves(const Geometry &g, int kind, size_t elem)
 {
-    constexpr long long kCus = 256;
-    const long long t = ((g.N + 1) / 2 + 15) / 16, b = t * t, rounds = (b + kCus - 1) / kCus;
-    const bool pairs = kind == ABG_BP_HAT || kind == ABG_BP_ADJ;
-    if (!sinogram_fits_offset(g.m(), elem) || 100 * b < (pairs ? 77 : 50) * kCus * rounds) return 0;
-    return b <= kCus ? 16 : 8;
+    return sinogram_fits_offset(g.m(), elem) ? orbit_waves(g.N, g.n_ang, kind, elem) : 0;
 }
 
 // x == nullptr: the padded copies in ws already hold the input.

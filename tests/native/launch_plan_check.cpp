@@ -79,6 +79,26 @@ int main()
     // fewer angles than a block takes, and none at all that fit
     CHECK(stage_fit(scan(64, 3, 1.0, 0).host, 64, 1.0, 4, 256) == 0.0);
     CHECK(stage_fit({}, 64, 1.0, 4, 256) == 0.0);
+    // back projections: orbits of four pixels where they are faster than tiles, in both types
+    for (int kind : {ABG_BP_HAT, ABG_BP_ADJ, ABG_BP_JOSEPH_T, ABG_BP_STRIP_T, ABG_BP_STRIP_TAU})
+        for (size_t elem : {4, 8})
+            for (int n_ang : {33, 720}) {
+                CHECK(orbit_waves(512, n_ang, kind, elem) == 16);
+                CHECK(orbit_waves(1024, n_ang, kind, elem) == 8);
+                CHECK(orbit_waves(2048, n_ang, kind, elem) == 8);
+                CHECK(orbit_waves(64, n_ang, kind, elem) == 0);
+                CHECK(orbit_waves(1, n_ang, kind, elem) == 0);
+            }
+    CHECK(orbit_waves(609, 180, ABG_BP_HAT, 4) == 0 && orbit_waves(897, 360, ABG_BP_HAT, 4) == 0);
+    CHECK(orbit_waves(672, 60, ABG_BP_HAT, 4) == 0 && orbit_waves(641, 180, ABG_BP_HAT, 4) == 8);
+    CHECK(orbit_waves(609, 60, ABG_BP_HAT, 8) == 0 && orbit_waves(609, 360, ABG_BP_HAT, 8) == 8);
+    CHECK(orbit_waves(817, 33, ABG_BP_ADJ, 4) == 0 && orbit_waves(1025, 60, ABG_BP_ADJ, 4) == 0);
+    CHECK(orbit_waves(929, 60, ABG_BP_ADJ, 4) == 8 && orbit_waves(1025, 65, ABG_BP_ADJ, 4) == 8);
+    for (int n_ang : {33, 60, 120, 360}) {
+        CHECK(orbit_waves(540, n_ang, ABG_BP_JOSEPH_T, 8) == 0 && orbit_waves(720, n_ang, ABG_BP_JOSEPH_T, 8) == 0);
+        CHECK(orbit_waves(720, n_ang, ABG_BP_JOSEPH_T, 4) == 8 && orbit_waves(720, n_ang, ABG_BP_STRIP_T, 8) == 8);
+        CHECK(orbit_waves(417, n_ang, ABG_BP_JOSEPH_T, 8) == (n_ang > 64 ? 16 : 0));
+    }
     std::printf("ok\n");
     return 0;
 }
