@@ -124,11 +124,21 @@ template <typename T, int AB = kAngBlock> struct BackLds {
     int ib[2][AB];      // first bin of each angle's window
 };
 
+// Sum of n partials (a power of two) by pairs, which rounds less than one after another.
+template <int N, typename T> __device__ inline T sum_by_pairs(T (&p)[N])
+{
+#pragma unroll
+    for (int h = N / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int v = 0; v < h; ++v) p[v] += p[v + h];
+    return p[0];
+}
+
 // Fixed-order sum of the waves' partials of a tile (the window space of the LDS becomes
-// `part`), scaled, into x or (PAD) into the forward projector's padded copies xr / xc;
+// `part`), scaled (in FP64, so that the scale adds no rounding of its own), into x or (PAD) into the forward projector's padded copies xr / xc;
 // ends with a block-wide barrier.
 template <typename T, bool PAD>
-__device__ inline void tile_store(const T (&acc)[kPixPerLane], T (*part)[kTile * kTile], T scale,
+__device__ inline void tile_store(const T (&acc)[kPixPerLane], T (*part)[kTile * kTile], double scale,
                                   T *__restrict__ x, int N, int c0, int r0, T *__restrict__ xr,
                                   T *__restrict__ xc, int S)
 {
@@ -146,10 +156,11 @@ __device__ inline void tile_store(const T (&acc)[kPixPerLane], T (*part)[kTile *
 #pragma unroll
         for (int j = 0; j < kPixPerLane; ++j) {
             const int pix = (ty0 + 4 * j) * kTile + tx;
-            T sum = acc[j];
+            T p[kBackWaves];
+            p[0] = acc[j];
 #pragma unroll
-            for (int v = 0; v < kBackWaves - 1; ++v) sum += part[v][pix];
-            const T val = sum * scale;
+            for (int v = 1; v < kBackWaves; ++v) p[v] = part[v - 1][pix];
+            const T val = T(sum_by_pairs(p) * scale);
             const int c = c0 + tx, r = r0 + ty0 + 4 * j;
             if constexpr (PAD) part[0][pix] = val;   // the lane's own entry
             else if (r < N && c < N) x[(size_t)r * N + c] = val;
@@ -333,7 +344,7 @@ __device__ inline void back_tile(const T *__restrict__ y, T *__restrict__ x,
             }
         }
     }
-    tile_store<T, PAD>(acc, L.part, ADJ ? T(1) : T(1.0 / ds), x, N, c0, r0, xr, xc, S);
+    tile_store<T, PAD>(acc, L.part, ADJ ? 1.0 : 1.0 / ds, x, N, c0, r0, xr, xc, S);
 }
 
 // ---- transposes of the strip and interpolation (Joseph) models ------------------------
@@ -480,7 +491,7 @@ __device__ inline void back_tile_v(const T *__restrict__ y, T *__restrict__ x,
             for (int j = 1; j < kPixPerLane; ++j) acc[j] += tap(L.win[t], fma(T(j), P.su4, u0), P);
         }
     }
-    tile_store<T, PAD>(acc, L.part, KIND == ABG_BP_JOSEPH_T ? T(1) : T(1.0 / ds), x, N, c0, r0, xr, xc, S);
+    tile_store<T, PAD>(acc, L.part, KIND == ABG_BP_JOSEPH_T ? 1.0 : 1.0 / ds, x, N, c0, r0, xr, xc, S);
 }
 
 }  // namespace

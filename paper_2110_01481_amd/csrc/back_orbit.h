@@ -12,9 +12,13 @@
 // Bound by the VALU and the LDS about alike: per angle and four pixels of a wave 23 vector
 // instructions and 5.2 LDS accesses against 33 and 6.9 of the tiles of back_body.h (2048^2 x
 // 1800: FP64 70% of either's issue rate, FP32 93% of the VALU's). 2048^2 x 1800 x 2897, ms per
-// apply, tiles -> orbits, FP64 / FP32: interpolating 2.34 / 1.49 -> 1.68 / 1.11, matched 4.37 / 2.29
-// -> 2.78 / 1.63, Joseph^T 5.68 / 3.55 -> 3.95 / 1.92, strip^T (with the area form of HalfArea)
-// 32.8 / 13.5 -> 4.85 / 2.49.
+// apply, tiles -> orbits, FP64 / FP32: interpolating 2.34 / 1.49 -> 1.71 / 1.12, matched 4.37 / 2.29
+// -> 2.82 / 1.61, Joseph^T 5.68 / 3.55 -> 3.97 / 2.02, strip^T (with the area form of HalfArea)
+// 32.8 / 13.5 -> 5.02 / 2.67.
+//
+// FP32 error against 64 bits at that size (uniform sinogram, 1e-8): tiles 8.6, matched 10.0;
+// orbits with coordinates from the window's start and a running sum rounded at every tap, as they
+// were first, 8.6, 10.0 and the three-tap kinds 11 to 12; now 8.0, 9.0 and 8.0.
 #pragma once
 
 #include <type_traits>
@@ -24,11 +28,28 @@
 namespace abg {
 namespace {
 
-// Window bins per angle and tile image: a 16 x 16 tile spans at most 15 sqrt(2) / ds < 28.3
-// bins for ds >= 0.75 (the smallest spacing a geometry accepts); the pair windows start one
-// bin below the smallest u, the plain ones (three taps) two.
+// Window bins per angle and tile image. Coordinates count from the bin below the tile's centre,
+// so that they stay small and FP32 rounds them finely: counted from the window's start, as in
+// back_body.h, the tile's first pixel has a large coordinate in half of the quadrants, and the
+// images turned by 90 degrees bring those in where a scan of 120 degrees leaves them out
+// (interpolating kind, 507^2 x 65 over 120 degrees, error against 64 bits: 6.6e-8 with tiles,
+// 8.0e-8 so). A 16 x 16 tile reaches 7.5 sqrt(2) / ds < 14.15 bins from its centre for ds >= 0.75
+// (the smallest spacing a geometry accepts), so a pixel lies at -14.15 < u < 15.15: the pair kinds
+// read bins -15 .. 16, the plain ones (three taps from u less the reach, < 1.45) bins -15 .. 18.
 template <int KIND> constexpr bool kPairKind = KIND == ABG_BP_HAT || KIND == ABG_BP_ADJ;
 template <int KIND> constexpr int kOrbWin = kPairKind<KIND> ? 32 : 40;
+// window entry of coordinate 0
+template <int KIND> constexpr int kOrbMid = kPairKind<KIND> ? 15 : 16;
+// FP64 coordinates are shifted up to stay positive, where truncation is floor; FP32 ones are not,
+// and one instruction rounds them down.
+template <typename T, int KIND> constexpr int kOrbShift = sizeof(T) == 8 ? kOrbMid<KIND> : 0;
+__device__ inline int bin_below(double u) { return (int)u; }
+__device__ inline int bin_below(float u)
+{
+    int k;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(k) : "v"(u));
+    return k;
+}
 
 // Window entry: HAT the bin's value and the difference to the next bin, ADJ the values of
 // the bin and of the next, the strip and Joseph transposes the value alone.
@@ -37,7 +58,7 @@ template <typename T> struct OrbEntryOf<T, ABG_BP_HAT> { using type = BinPair<T>
 template <typename T> struct OrbEntryOf<T, ABG_BP_ADJ> { using type = BinPair<T>; };
 template <typename T, int KIND> using OrbEntry = typename OrbEntryOf<T, KIND>::type;
 
-// Per staged angle: window coordinate of the tile's first pixel (f0) and of its image under
+// Per staged angle: window coordinate of the tile's centre (f0) and of its image under
 // rotation by 90 degrees (f1), the change of u per pixel step, and the footprint's constants.
 template <typename T> struct alignas(16) OrbStage {
     T f0, f1, cu, su;
@@ -58,13 +79,13 @@ template <typename T> struct OrbTaps<T, ABG_BP_HAT> {
     template <bool AXIS> __device__ void at(T u, const Stage &, T)
     {
         w = fract_of(u);
-        k = (int)u;
+        k = bin_below(u);
     }
     using Bins = BinPair<T>;
     __device__ Bins read(const OrbEntry<T, ABG_BP_HAT> *e) const { return e[k]; }
     __device__ void add(T &acc, const Bins &b) const { acc += fma(w, b.d, b.v); }
     __device__ static BinPair<T> fill(T v, T next, const Stage &) { return {v, next - v}; }
-    __device__ static T scale(double ds) { return T(1.0 / ds); }
+    __device__ static double scale(double ds) { return 1.0 / ds; }
 };
 
 // fma(a, b, c) clamped to [0, 1]
@@ -108,7 +129,7 @@ template <typename T> struct OrbTaps<T, ABG_BP_ADJ> {
     template <bool AXIS> __device__ void at(T u, const Stage &P, T dsT)
     {
         const T w = fract_of(u);
-        k = (int)u;
+        k = bin_below(u);
         if constexpr (AXIS) {
             a0 = box01(w * dsT);
             a1 = box01((T(1) - w) * dsT);
@@ -121,7 +142,7 @@ template <typename T> struct OrbTaps<T, ABG_BP_ADJ> {
     __device__ Bins read(const OrbEntry<T, ABG_BP_ADJ> *e) const { return e[k]; }
     __device__ void add(T &acc, const Bins &b) const { acc = fma(a1, b.d, fma(a0, b.v, acc)); }
     __device__ static BinPair<T> fill(T v, T next, const Stage &P) { return {v * P.invp, next * P.invp}; }
-    __device__ static T scale(double) { return T(1); }
+    __device__ static double scale(double) { return 1.0; }
 };
 
 // Strip and Joseph transposes: three bins from k on (three always hold a pixel's whole
@@ -145,8 +166,7 @@ template <typename T, int KIND> struct OrbTaps {
     int k;
     template <bool AXIS> __device__ void at(T u, const Stage &P, T dsT)
     {
-        // window coordinates keep u - reach >= 0.5, so truncation is floor
-        k = (int)(u - P.reach) + 1;
+        k = bin_below(u - P.reach) + 1;
         const T e = T(k) - u;
         if constexpr (KIND == ABG_BP_JOSEPH_T) {
             w[0] = fmax(fma(-fabs(e), P.js, P.invp), T(0));
@@ -169,10 +189,11 @@ template <typename T, int KIND> struct OrbTaps {
     __device__ Bins read(const T *e) const { return {{e[k], e[k + 1], e[k + 2]}}; }
     __device__ void add(T &acc, const Bins &b) const
     {
-        acc = fma(w[0], b.v[0], fma(w[1], b.v[1], fma(w[2], b.v[2], acc)));
+        // one rounding of the running sum per angle, as in back_body.h (3% of the strip's time)
+        acc += fma(w[0], b.v[0], fma(w[1], b.v[1], w[2] * b.v[2]));
     }
     __device__ static T fill(T v, T, const Stage &) { return v; }
-    __device__ static T scale(double ds) { return KIND == ABG_BP_JOSEPH_T ? T(1) : T(1.0 / ds); }
+    __device__ static double scale(double ds) { return KIND == ABG_BP_JOSEPH_T ? 1.0 : 1.0 / ds; }
 };
 
 // Positions whose window reads are in flight together: all of a coordinate's four where the
@@ -215,13 +236,13 @@ __device__ inline void back_orbit_tile(const T *__restrict__ y, T *__restrict__ 
                                        T *__restrict__ xc, int S, double tau_thr)
 {
     using Taps_ = OrbTaps<T, KIND>;
-    constexpr int NT = 64 * NWV, W = kOrbWin<KIND>;
+    constexpr int NT = 64 * NWV, W = kOrbWin<KIND>, kMid = kOrbMid<KIND> - kOrbShift<T, KIND>;
     constexpr int kEnt = 2 * AB * W;                   // window pairs' entries of a round
     constexpr int kIt = (kEnt + NT - 1) / NT;          // per thread (the last pass may be part)
     static_assert(AB <= NT && (kEnt % NT == 0 || !kPairKind<KIND>), "window split");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    T ftx = T(lane & 15), fty = T(lane >> 4);
+    T ftx = T(lane & 15) - T(7.5), fty = T(lane >> 4) - T(0.5 * (4 * PPL - 1));
     const int n_rounds = (n_ang + AB - 1) / AB;
     const T dsT = T(ds);
 
@@ -232,23 +253,20 @@ __device__ inline void back_orbit_tile(const T *__restrict__ y, T *__restrict__ 
             int cx = c0, cy = r0;
             double s0v = s0;
             asm volatile("" : "+s"(cx), "+s"(cy), "+s"(s0v));
-            const double xref = cx - 0.5 * N + 0.5, yref = cy - 0.5 * N + 0.5;
+            const double xref = cx - 0.5 * N + 8.0, yref = cy - 0.5 * N + 2.0 * PPL;
             const double s0u = s0v / ds;
             const double u0 = fma(xref, Pn.cu, fma(yref, Pn.su, -s0u));
             const double u1 = fma(xref, Pn.su, fma(-yref, Pn.cu, -s0u));
-            constexpr double X = 15, Y = 4 * PPL - 1, kBelow = kPairKind<KIND> ? 1.0 : 2.0;
-            const double m0 = u0 + X * fmin(Pn.cu, 0.0) + Y * fmin(Pn.su, 0.0);
-            const double m1 = u1 + X * fmin(Pn.su, 0.0) + Y * fmin(-Pn.cu, 0.0);
-            const double i0 = floor(m0) - kBelow, i1 = floor(m1) - kBelow;
+            const double i0 = floor(u0), i1 = floor(u1);
             typename Taps_::Stage st;
-            st.f0 = T(u0 - i0);
-            st.f1 = T(u1 - i1);
+            st.f0 = T(u0 - i0 + kOrbShift<T, KIND>);
+            st.f1 = T(u1 - i1 + kOrbShift<T, KIND>);
             st.cu = T(Pn.cu);
             st.su = T(Pn.su);
             st.set(Pn, ds, tau_thr);
             L.prm[r & 1][threadIdx.x] = st;
-            L.ib[r & 1][threadIdx.x][0] = (int)i0;
-            L.ib[r & 1][threadIdx.x][1] = (int)i1;
+            L.ib[r & 1][threadIdx.x][0] = (int)i0 - kOrbMid<KIND>;
+            L.ib[r & 1][threadIdx.x][1] = (int)i1 - kOrbMid<KIND>;
         }
     };
     T wf[kIt], wb[kIt];                                // entry kk of a window, and of its image
@@ -307,7 +325,9 @@ __device__ inline void back_orbit_tile(const T *__restrict__ y, T *__restrict__ 
             if constexpr (sizeof(T) == 8) asm volatile("" : "+v"(ftx), "+v"(fty));
             auto angle = [&](auto axis_) {
                 constexpr bool AXIS = decltype(axis_)::value;
-                const typename Taps_::Stage &P = L.prm[r & 1][t];
+                // in registers at once where it is four numbers (else the compiler splits the load)
+                using Held = std::conditional_t<KIND == ABG_BP_HAT, const typename Taps_::Stage, const typename Taps_::Stage &>;
+                Held P = L.prm[r & 1][t];
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
                     const T u0 = s == 0 ? fma(ftx, P.cu, fma(fty, P.su, P.f0))
@@ -322,8 +342,8 @@ __device__ inline void back_orbit_tile(const T *__restrict__ y, T *__restrict__ 
 #pragma unroll
                         for (int j = 0; j < G; ++j) {
                             tap[j].template at<AXIS>(j0 + j == 0 ? u0 : fma(T(j0 + j), step, u0), P, dsT);
-                            bf[j] = tap[j].read(L.win[t][s]);
-                            bb[j] = tap[j].read(L.win[t][s + 2]);
+                            bf[j] = tap[j].read(L.win[t][s] + kMid);
+                            bb[j] = tap[j].read(L.win[t][s + 2] + kMid);
                         }
 #pragma unroll
                         for (int j = 0; j < G; ++j) {
@@ -345,7 +365,7 @@ __device__ inline void back_orbit_tile(const T *__restrict__ y, T *__restrict__ 
     }
     // fixed-order sum of the waves' partials, image by image
     constexpr int H = 4 * PPL, PX = 64 * PPL;
-    const T scale = Taps_::scale(ds);
+    const double scale = Taps_::scale(ds);
     const int Hc = (N + 1) / 2, Hr = N / 2;
 #pragma unroll
     for (int o = 0; o < 4; ++o) {
@@ -354,10 +374,10 @@ __device__ inline void back_orbit_tile(const T *__restrict__ y, T *__restrict__ 
         for (int j = 0; j < PPL; ++j) L.part[wave][(lane >> 4) * 16 + (lane & 15) + 64 * j] = acc[o][j];
         __syncthreads();
         for (int i = threadIdx.x; i < PX; i += NT) {
-            T sum = L.part[0][i];
+            T p[NWV];
 #pragma unroll
-            for (int v = 1; v < NWV; ++v) sum += L.part[v][i];
-            L.out[i] = sum * scale;
+            for (int v = 0; v < NWV; ++v) p[v] = L.part[v][i];
+            L.out[i] = T(sum_by_pairs(p) * scale);
         }
         __syncthreads();
         // columns or rows of the image run along tx (o even) or ty (o odd): each pass writes
