@@ -104,18 +104,21 @@ inline FwdPlan plan_forward(const Geometry &g, size_t elem, int forced_lg, int s
 // percent: the tiles over four times 256 CUs times the orbit blocks of the busiest CU. Up to 64
 // angles the tiles fill one window each and the orbits' setting up counts for more. The orbits
 // are taken where they are faster (us per apply, tiles / orbits; N^2 x angles, even):
-//  - interpolating, FP32: 672 x 60, 86, 8.6 / 9.0; 817 x 60, 88, 12.4 / 12.0; 609 x 180, 74,
-//    17.6 / 19.5; 897 x 180, 79, 32.4 / 34.5; 641 x 180, 82, 19.9 / 19.6; 512 x 720, 100, 43 / 38;
-//    1024 x 720, 100, 147 / 123. FP64: 609 x 60, 74, 11.2 / 11.7, x 360 48.0 / 47.4; 433 x 60, 76,
-//    7.9 / 8.5, x 360 34.1 / 28.0; 1025 x 60, 82, 26.2 / 25.2.
-//  - matched, FP32: 817 x 33, 88, 13.0 / 13.9; 1169 x 33, 89, 23.3 / 23.5; 641 x 60, 82, 11.8 /
-//    11.5; 1025 x 60, 82, 24.5 / 25.1; 929 x 60, 84, 20.8 / 20.5; 609 x 120, 74, 18.5 / 18.7;
-//    897 x 180, 79, 49.7 / 48.2; 1249 x 180, 87, 90.6 / 80.7. FP64: 609 x 60, 74, 18.4 / 17.7; 881 x
+//  - interpolating, FP32: 672 x 60, 86, 9.2 / 9.5; 817 x 60, 88, 13.5 / 12.7; 609 x 180, 74,
+//    18.5 / 19.5; 640 x 720, 78, 67.6 / 64.6; with more blocks per CU 769 x 180, 78, 26.1 / 26.5 and
+//    897 x 180, 79, 32.6 / 34.2; 512 x 720, 100, 43 / 39; 1024 x 720, 100, 147 / 122. FP64: 609 x 60,
+//    74, 11.1 / 11.7, x 360 48.0 / 47.9; 433 x 60, 76, 7.8 / 8.5, x 360 34.1 / 28.0; 1025 x 60, 82,
+//    26.1 / 25.4.
+//  - matched, FP32: 817 x 33, 88, 13.1 / 13.4; 1169 x 33, 89, 23.3 / 23.0; 641 x 60, 82, 11.8 /
+//    11.6; 1025 x 60, 82, 24.5 / 24.5; 929 x 60, 84, 20.8 / 20.2; 609 x 120, 74, 18.5 / 18.6;
+//    897 x 180, 79, 49.8 / 47.3; 1249 x 180, 87, 90.4 / 79.0. FP64: 609 x 60, 74, 18.2 / 17.7; 881 x
 //    360, 76, 186 / 149.
-//  - Joseph^T, FP64, one block per CU: 417 x 60, 71, 13.3 / 13.9; 448 x 60, 76, 15.9 / 13.4; 384 x
-//    120, 56, 21.9 / 22.2, x 360 60.4 / 57.2; more: 720 x 360, 65, 154 / 165; 577 x 360, 66,
-//    116 / 108. FP32: 384 x 360, 56, 40.9 / 33.2; 720 x 33, 65, 15.4 / 13.9.
-//  - the strip kinds' tiles take two to four times as long.
+//  - Joseph^T, FP64: 417 x 360, 71, 55.0 / 57.2; 448 x 360, 76, 70.1 / 57.5; 609 x 360, 74, 104 /
+//    108; 896 x 360, 76, 219 / 210; three blocks per CU, of which two are resident, 768 x 360, 75,
+//    154 / 165. FP32: 417 x 60, 71, 8.4 / 8.8, x 360 34.4 / 33.4; 448 x 60, 76, 10.1 / 8.7; 544 x
+//    360, 56, 53.5 / 55.6; 573 x 309, 63, 54.0 / 49.3.
+//  - strip^T and B_tau, FP64: 417 x 60, 71, 16.3 / 16.6, x 360 82.2 / 75.6; 544 x 360, 56, 132 / 137;
+//    577 x 360, 66, 156 / 137. FP32: 384 x 60, 56, 10.8 / 10.4; 544 x 360, 56, 79 / 72.
 // One block per CU or less takes 16 waves (512^2 FP64 58 with 8, 51 with 16), more blocks 8.
 inline int orbit_waves(int N, int n_ang, int kind, size_t elem)
 {
@@ -124,9 +127,10 @@ inline int orbit_waves(int N, int n_ang, int kind, size_t elem)
     const long long tiles = (N + 15) / 16, even = 100 * tiles * tiles / (4 * kCus * per_cu);
     const bool few = n_ang <= 64, f64 = elem == 8;
     long long least = 50;
-    if (kind == ABG_BP_HAT) least = f64 ? (few ? 80 : 74) : few ? 87 : 80;
+    if (kind == ABG_BP_HAT) least = f64 ? (few ? 80 : 74) : few ? 87 : per_cu <= 2 ? 77 : 80;
     else if (kind == ABG_BP_ADJ) least = f64 ? 74 : n_ang <= 40 ? 89 : few ? 84 : 75;
-    else if (kind == ABG_BP_JOSEPH_T && f64) least = per_cu > 1 ? 66 : few ? 75 : 50;
+    else if (kind == ABG_BP_JOSEPH_T && f64) least = per_cu == 3 ? 81 : 76;
+    else if (kind == ABG_BP_JOSEPH_T || f64) least = per_cu > 1 ? 60 : few ? 76 : 50;
     if (even < least) return 0;
     return per_cu == 1 ? 16 : 8;
 }

@@ -89,15 +89,20 @@ int main()
                 CHECK(orbit_waves(64, n_ang, kind, elem) == 0);
                 CHECK(orbit_waves(1, n_ang, kind, elem) == 0);
             }
+    CHECK(orbit_waves(640, 720, ABG_BP_HAT, 4) == 8 && orbit_waves(769, 180, ABG_BP_HAT, 4) == 0);
     CHECK(orbit_waves(609, 180, ABG_BP_HAT, 4) == 0 && orbit_waves(897, 360, ABG_BP_HAT, 4) == 0);
     CHECK(orbit_waves(672, 60, ABG_BP_HAT, 4) == 0 && orbit_waves(641, 180, ABG_BP_HAT, 4) == 8);
     CHECK(orbit_waves(609, 60, ABG_BP_HAT, 8) == 0 && orbit_waves(609, 360, ABG_BP_HAT, 8) == 8);
     CHECK(orbit_waves(817, 33, ABG_BP_ADJ, 4) == 0 && orbit_waves(1025, 60, ABG_BP_ADJ, 4) == 0);
     CHECK(orbit_waves(929, 60, ABG_BP_ADJ, 4) == 8 && orbit_waves(1025, 65, ABG_BP_ADJ, 4) == 8);
     for (int n_ang : {33, 60, 120, 360}) {
-        CHECK(orbit_waves(540, n_ang, ABG_BP_JOSEPH_T, 8) == 0 && orbit_waves(720, n_ang, ABG_BP_JOSEPH_T, 8) == 0);
+        for (int N : {384, 417, 540, 609, 720, 768}) CHECK(orbit_waves(N, n_ang, ABG_BP_JOSEPH_T, 8) == 0);
+        CHECK(orbit_waves(448, n_ang, ABG_BP_JOSEPH_T, 8) == 16 && orbit_waves(896, n_ang, ABG_BP_JOSEPH_T, 8) == 8);
+        CHECK(orbit_waves(417, n_ang, ABG_BP_JOSEPH_T, 4) == (n_ang > 64 ? 16 : 0));
+        CHECK(orbit_waves(417, n_ang, ABG_BP_STRIP_TAU, 8) == (n_ang > 64 ? 16 : 0));
+        CHECK(orbit_waves(544, n_ang, ABG_BP_JOSEPH_T, 4) == 0 && orbit_waves(544, n_ang, ABG_BP_STRIP_T, 8) == 0);
         CHECK(orbit_waves(720, n_ang, ABG_BP_JOSEPH_T, 4) == 8 && orbit_waves(720, n_ang, ABG_BP_STRIP_T, 8) == 8);
-        CHECK(orbit_waves(417, n_ang, ABG_BP_JOSEPH_T, 8) == (n_ang > 64 ? 16 : 0));
+        CHECK(orbit_waves(384, n_ang, ABG_BP_STRIP_T, 4) == 16 && orbit_waves(544, n_ang, ABG_BP_STRIP_T, 4) == 8);
     }
     std::printf("ok\n");
     return 0;
