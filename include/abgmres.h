@@ -332,8 +332,8 @@ int abg_engine_poll(abg_engine *e, long long *tags, int *status, int max, int *n
  * 0 deals the items out round-robin over the resident blocks; 1 cuts each
  * item list into 8 contiguous ranges, one per XCD, that blocks drain through per-range
  * counters in shrinking chunks (half of what is left over the blocks of the range) before
- * helping with the others; 2 (the default) hands the whole list out in order through one
- * counter, in shrinking chunks, so that all blocks work on the same one or two problems
+ * helping with the others; 2 (the default) hands the whole list out in order, one item at a
+ * time through 32 counters, so that all blocks work on the same one or two problems
  * at a time.
  * Results do not depend on any of them. */
 int abg_engine_set_tiles(abg_engine *e, int rays, int ang_block, int sched);
@@ -377,21 +377,22 @@ int abg_ncp_force_goertzel(int on);
 /* Block shape of the forward projectors (line, strip and Joseph models): each block of
  * 256 threads takes 2^lg_angles consecutive angles and 256 / 2^lg_angles consecutive rays
  * of each (0: one angle, 1: two, 2: four). -1 (the default) chooses by the geometry; the
- * line model then takes 64 rays of four or eight angles per block wherever the launch is
- * large enough (four-angle blocks, and those of eight, stage their band rows in LDS;
- * below), else, like the other models, four angles for N > 512 and one, or two where that
+ * line and Joseph models then take 64 rays of four or eight angles per block wherever the
+ * launch is large enough (four-angle blocks, and those of eight, stage their band rows in
+ * LDS; below), else, like the strip model, four angles for N > 512 (one where that spreads a
+ * launch that does not fill the device better) and one, or two where that
  * leaves fewer lanes of the last block of each angle idle. The shape changes only
  * which rays run together, never a ray's arithmetic: results are bit-identical for every
  * shape. Process-wide; for tests and measurements. Returns ABG_OK, or ABG_EINVAL for
  * lg_angles outside -1..2. */
 int abg_fp_force_block_shape(int lg_angles);
 
-/* Share of the forward-projector blocks of four or eight angles (line model) that stage
- * each band row's columns in LDS and read their taps there, in eighths (0..8), spread over
- * the grid; the other blocks read their taps from the image copies. -1 (the default)
- * restores the automatic share, all of them. Results are
- * bit-identical for every share. Process-wide; for tests and measurements. Returns ABG_OK, or ABG_EINVAL
- * for eighths outside -1..8. */
+/* Share of the forward-projector blocks of four or eight angles (line and Joseph models)
+ * that stage each band row's columns in LDS and read their taps there, in eighths (0..8),
+ * spread over the grid; the other blocks, and those whose rays do not fit one window, read
+ * their taps from the image copies. -1 (the default) restores the automatic share, all of
+ * them. Results are bit-identical for every share. Process-wide; for tests and measurements.
+ * Returns ABG_OK, or ABG_EINVAL for eighths outside -1..8. */
 int abg_fp_force_stage_share(int eighths);
 
 /* Releases what the library holds process-wide beyond geometries and engines: the

@@ -131,7 +131,6 @@ struct MgsLaunch {
     DevState *st;
     double bd_rel;               // breakdown: h_{k+1,k} <= bd_rel * ||q_k||
     int step;                    // Arnoldi step (0: the initial normalisation)
-    // single solves only (zero otherwise)
     int set_beta;                // step 0: beta = h_{1,0}, or the zero-right-hand-side stop
     // step k >= 1: the Givens update of column k follows in the same launch (giv_H null:
     // none); arguments as for launch_givens, beta read from st; snap as for launch_combine
@@ -177,7 +176,6 @@ hipError_t launch_sub_norm(int t, const void *a, const void *b, void *out, long 
 hipError_t launch_givens(double *H, int ld, double *R, double *cs, double *sn, double *g,
                          double *y, double *rho, const double *beta, int k, DevState *st,
                          hipStream_t s, DevState *snap = nullptr);
-// st->beta = st->hnext after the initial normalisation, or the zero-right-hand-side stop.
 // Clears the stop flag (after a DP candidate that the explicit residual rejected).
 hipError_t launch_clear_stop(DevState *st, hipStream_t s);
 void set_mgs_target_blocks(int blocks);
@@ -278,7 +276,6 @@ struct InstanceView {
     double *H, *R, *cs, *sn, *g, *Y, *rho, *part, *mgs_part, *q64, *gram;
     unsigned *count;
     long long L, ldv, mp, np;
-    int part_cap;                 // doubles in part
     int mgs_rows;                 // rows per MGS slot table
     long long mgs_part_cap;       // doubles in mgs_part (two tables)
 };

@@ -163,7 +163,7 @@ template <> struct Band<double> {
     __device__ void next() { lo += m; }
     // padded column, unclamped, by truncation. A wave walks only bands near those some
     // lane's ray crosses (at most N of them, |m| <= 1), and the lanes of a wave lie within
-    // 63 bins of each other (63 * 64 * sqrt(2) < 5702 px for the spacings a geometry
+    // 63 bins of each other (63 * 64 * sqrt(2) < 5703 px for the spacings a geometry
     // accepts), so every column a walking lane reaches is below 2N + 5720 < 2^17 in
     // magnitude (N <= 32768): the conversion is exact and the byte offset cannot wrap back
     // into the row. A tap can meet a nonzero pixel only for lo >= kPad - 1 > 0, where
@@ -459,13 +459,12 @@ struct FwdOrder {
 
 // ---- several angles per block, band rows staged in LDS (line and Joseph models) -----------
 // The forward walk above issues one 64-lane gather per band and wave, and the texture
-// path takes them at four lane addresses per cycle: that rate bounds it. A block of four
-// adjacent angles (one wave each) and the same 64 rays reads nearly the same columns of
-// every band row in all four waves, so here each band row's columns the block can touch
-// are copied once into LDS by one 16-byte load per lane (a quarter of the addresses), and
-// the waves read their taps from there. Everything else is the walk above, band by band
-// in the same order: the results are the same bits. Run beside the direct walk in the
-// same launch it takes its taps through the other unit.
+// path takes them at four lane addresses per cycle: that rate bounds it. A block of NW
+// consecutive angles (one wave each) and the same 64 rays reads nearly the same columns of
+// every band row in all its waves, so here each band row's columns the block can touch
+// are copied once into LDS by one 16-byte load per lane, and the waves read their taps from
+// there. Everything else is the walk above, band by band in the same order: the results are
+// the same bits.
 //
 // The window of a group of kChunk bands holds kStageCols columns from org. For angle i the
 // leftmost lane sits at lmin_i + r m_i and the rightmost at rmax_i + r m_i (padded
@@ -499,8 +498,8 @@ __device__ inline long long uniform_ll(long long v)
     return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
-// Angles a0 .. a0 + 3 (wave w takes a0 + w), rays ray0 .. ray0 + 63 of each. All four
-// waves call it (also for angles past n_ang); it starts with a block-wide barrier, so
+// Angles a0 .. a0 + NW - 1 (wave w takes a0 + w), rays ray0 .. ray0 + 63 of each; TRIP: bands
+// per trip of a block that walks directly. All NW waves call it (also for angles past n_ang); it starts with a block-wide barrier, so
 // that consecutive calls of a block may share L.
 template <typename T, int NW, int MODEL = ABG_FP_LINE, int TRIP = kChunk>
 __device__ inline void forward_block_staged(const T *__restrict__ xr, const T *__restrict__ xc,

@@ -202,6 +202,13 @@ __device__ inline double gather_total(const double *slots, int G, double *lds, i
 // kGatherRows rows at once, so the rows of one exchange cost one round of polling
 // together; the waves' sums are added in wave order. Larger groups: gather_total row by
 // row. Bounded wait as gather_total.
+//
+// What both waits rely on. Every rank of the group runs, or starts without waiting for it
+// (the share of the device that launch_mgs asks for). A slot is written once per step, after
+// the step before cleared it: the same rank of a group of the same size, in an earlier launch.
+// Slots are read with device-scope loads only; a plain load may see the XCD's own L2 for ever.
+// The waves of a block leave a poll together (one barrier per poll): `red` and `lds` are then
+// free for the next chunk, and a wait that is used up is left by the whole block.
 __device__ inline void gather_rows(const double *tab, int G, int R, double (*red)[kGatherRows],
                                    double *tot, double *lds, int *err)
 {
@@ -280,8 +287,8 @@ __device__ inline void gather_rows(const double *tab, int G, int R, double (*red
 // apart whatever G is (step 0 and the later steps of a batched solve run with different
 // groups, and a group must not find another's partials in its own table); step k uses
 // table k & 1, row i for <q, w_i>, row k for ||q||^2 after the sweep and row k + 1 for
-// ||q_k||^2 before it. Each rank clears its own column of the other table (rows up to
-// k + 2) for the next step; both tables start cleared.
+// ||q_k||^2 before it (the low-synchronisation form: below). Each rank clears its own column
+// of the other table, the rows that the next step can use; both tables start cleared.
 // The Givens update that follows Gram-Schmidt step k, done by the block of rank 0 once
 // h_{1..k+1,k} are known (H null: none).
 struct GivensDev {

@@ -57,8 +57,7 @@ struct FwdShape {
 };
 
 // Line and Joseph models, NW angles per block, band rows staged in LDS
-// (forward_block_staged): bound by
-// the VALU (8 instructions per band, wave and ray; 83% busy at 2048^2 x 1800 in FP64) beside
+// (forward_block_staged): bound by the VALU (8 instructions per band, wave and ray; 83% busy at 2048^2 x 1800 in FP64) beside
 // 8 cycles of LDS reads per band and wave. 2048^2 x 1800 x 2897: FP64 3.20 -> 2.07 ms, FP32
 // 2.77 -> 1.58 ms against the direct walk with the staged share it had; L2 fills 15.4 -> 5.0 GB
 // (FP64), gathers 1.1e8 -> 1.6e7 per launch. A share
@@ -105,7 +104,8 @@ __global__ __launch_bounds__(kFwdBlock) void forward_kernel(
 // (measured faster than 128 on large images, equal on small ones).
 constexpr int kSingleAngBlock = 64;
 
-// PAD: x is the forward projector's scratch (padded copies written directly).
+// The back kernels with PAD: x is the forward projector's scratch (padded copies written
+// directly).
 
 // Transposes of the strip and interpolation models (KIND ABG_BP_STRIP_T / _JOSEPH_T) and
 // the thresholded strip transpose (ABG_BP_STRIP_TAU, entries below tau_thr dropped).

@@ -480,7 +480,6 @@ InstanceView instance_view(const Geometry &g, int method, int k_max, abg_precisi
     v.ldv = ly.ldv;
     v.mp = ly.mp;
     v.np = ly.np;
-    v.part_cap = 2048;
     v.mgs_rows = ly.mgs_rows;
     v.mgs_part_cap = ly.mgs_cap;
     return v;
