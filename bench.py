@@ -86,7 +86,7 @@ def _counter_means(csv_path: str, kernel_prefix) -> dict:
 def summarize_counters(d: str, kernel_key: str = "forward_kernel_f32",
                        workload: str = "512x512, 720 x 725, FP32", bench_args: str = "") -> str:
     """Markdown summary of the FETCH_SIZE / WRITE_SIZE passes under directory d (sub-
-    directories fetch, write, cfetch, cwrite, and optionally sq and l2, as written by the
+    directories fetch, write, cfetch, cwrite, and optionally sq, lds and l2, as written by the
     commands listed in it) for the kernel `kernel_key` of COUNTER_KERNELS."""
     prefixes = COUNTER_KERNELS[kernel_key][0]
     kname = " / ".join(prefixes)
@@ -111,6 +111,15 @@ def summarize_counters(d: str, kernel_key: str = "forward_kernel_f32",
         data["valu_wave_insts_per_dispatch"] = round(sq["SQ_INSTS_VALU"], 1)
         if "SQ_INSTS_VMEM_RD" in sq:
             data["vmem_read_wave_insts_per_dispatch"] = round(sq["SQ_INSTS_VMEM_RD"], 1)
+        # issue cycles (counted in fours) over those of 256 CUs x 4 SIMDs; GRBM_GUI_ACTIVE adds
+        # the cycles of the 8 XCDs
+        if sq.get("GRBM_GUI_ACTIVE", 0.0) > 0.0:
+            data["valu_busy"] = round(4.0 * sq["SQ_ACTIVE_INST_VALU"] / (1024.0 * sq["GRBM_GUI_ACTIVE"] / 8.0), 3)
+    lds_csv = os.path.join(d, "lds", "run_counter_collection.csv")
+    if os.path.exists(lds_csv):
+        ld = _counter_means(lds_csv, prefixes)
+        if ld.get("GRBM_GUI_ACTIVE", 0.0) > 0.0:
+            data["lds_busy"] = round(ld["SQ_LDS_IDX_ACTIVE"] / (256.0 * ld["GRBM_GUI_ACTIVE"] / 8.0), 3)
     l2_csv = os.path.join(d, "l2", "run_counter_collection.csv")
     if os.path.exists(l2_csv):
         # L2 (TCC) hit rate = hits / (hits + misses) per kernel of the solve
@@ -124,6 +133,7 @@ def summarize_counters(d: str, kernel_key: str = "forward_kernel_f32",
     c = "python -u bench.py --copy-calibration-mib 1024"
     sqc = ("SQ_WAVES SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_INSTS_VALU SQ_INSTS_VMEM_RD "
            "SQ_ACTIVE_INST_VALU SQ_WAIT_ANY GRBM_GUI_ACTIVE")
+    ldc = "SQ_INSTS_LDS SQ_LDS_IDX_ACTIVE SQ_LDS_BANK_CONFLICT GRBM_GUI_ACTIVE"
     lines = [
         f"# HBM traffic of {kname} ({workload})",
         "",
@@ -139,12 +149,16 @@ def summarize_counters(d: str, kernel_key: str = "forward_kernel_f32",
         f"    rocprofv3 --pmc FETCH_SIZE --output-format csv -d <dir>/cfetch -o run -- {c}",
         f"    rocprofv3 --pmc WRITE_SIZE --output-format csv -d <dir>/cwrite -o run -- {c}",
         f"    rocprofv3 --pmc {sqc} --output-format csv -d <dir>/sq -o run -- {b}",
+        f"    rocprofv3 --pmc {ldc} --output-format csv -d <dir>/lds -o run -- {b}",
         f"    rocprofv3 --pmc TCC_HIT_sum TCC_MISS_sum --output-format csv -d <dir>/l2 -o run -- {b}",
         f"    python bench.py --summarize-counters <dir> --counter-kernel {kernel_key}",
         "",
         "The SQ pass gives the VALU instructions per dispatch (wave level; x 64 lanes for",
-        "the lane operations that bench.py sets against the VALU issue rate); the TCC pass",
-        "the L2 hit rate, hits / (hits + misses), of each kernel of the solve.",
+        "the lane operations that bench.py sets against the VALU issue rate) and the share of",
+        "the SIMDs' cycles, at the clock of the run, in which one issues (`valu_busy`: four",
+        "cycles each; some FP32 instructions take two, so that its reading is an upper bound);",
+        "the LDS pass the same share for the CUs' LDS (`lds_busy`); the TCC pass the L2 hit rate,",
+        "hits / (hits + misses), of each kernel of the solve.",
         "",
         "`source_hash` covers the kernel's sources; bench.py reports `traffic` only while it",
         "matches.",

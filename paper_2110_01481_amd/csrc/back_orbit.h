@@ -11,7 +11,9 @@
 //
 // Bound by the VALU and the LDS about alike: per angle and four pixels of a wave 23 vector
 // instructions and 5.2 LDS accesses against 33 and 6.9 of the tiles of back_body.h (2048^2 x
-// 1800: FP64 70% of either's issue rate, FP32 93% of the VALU's). 2048^2 x 1800 x 2897, ms per
+// 1800: FP64 69% of either's issue rate, FP32 86% of the LDS's and at most 94% of the VALU's).
+// At 512^2 x 720 in FP32, with one block per CU, neither is: 48% and at most 54%, as nothing else
+// on the CU covers the phases between the block's barriers. 2048^2 x 1800 x 2897, ms per
 // apply, tiles -> orbits, FP64 / FP32: interpolating 2.34 / 1.49 -> 1.71 / 1.12, matched 4.37 / 2.29
 // -> 2.82 / 1.61, Joseph^T 5.68 / 3.55 -> 3.97 / 2.02, strip^T (with the area form of HalfArea)
 // 32.8 / 13.5 -> 5.02 / 2.67.

@@ -57,8 +57,8 @@ struct FwdShape {
 };
 
 // Line and Joseph models, NW angles per block, band rows staged in LDS
-// (forward_block_staged): bound by the VALU (8 instructions per band, wave and ray; 83% busy at 2048^2 x 1800 in FP64) beside
-// 8 cycles of LDS reads per band and wave. 2048^2 x 1800 x 2897: FP64 3.20 -> 2.07 ms, FP32
+// (forward_block_staged): bound by the VALU (8 instructions per band, wave and ray; 85% busy at
+// 2048^2 x 1800 in FP64), then by the LDS (70%). 2048^2 x 1800 x 2897: FP64 3.20 -> 2.07 ms, FP32
 // 2.77 -> 1.58 ms against the direct walk with the staged share it had; L2 fills 15.4 -> 5.0 GB
 // (FP64), gathers 1.1e8 -> 1.6e7 per launch. A share
 // of the blocks below eight eighths (tests and measurements; spread over the grid by a hash
